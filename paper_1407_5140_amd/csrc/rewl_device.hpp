@@ -159,6 +159,24 @@ __device__ __forceinline__ int decide_fast(double delta, double vb, double band)
     return delta > vb ? 1 : (delta >= vb - 2.0 * band ? 2 : 0);
 }
 
+// Bounds of that test in FP32: for the draw u53 of words (z, w), delta > hi is
+// certain to accept and delta < lo certain to reject by decide_fast with the given
+// band, so only a delta between them needs the FP64 logarithm (about one attempt
+// in 10^5).  u = u53 2^-53 enters as fma(z, 2^-32, w) 2^-32, off by less than
+// 2^-20 u for w > 0, and v_log_f32 is within 2^-23 (1 + |log2 u|) of log2 u at
+// every float in [2^-60, 1] (all of them compared); the bounds leave 2^-19 + 2^-20 |log u|.  w = 0 leaves every finite delta open.
+struct Bound32 {
+    float lo, hi;
+};
+__device__ __forceinline__ Bound32 bounds_of(uint32_t z, uint32_t w, float band)
+{
+    const float u = __builtin_fmaf((float)z, 0x1p-32f, (float)w) * 0x1p-32f;
+    const float l2 = __builtin_amdgcn_logf(u), e = 0x1p-19f + band;
+    const float lo = __builtin_fmaf(l2, 0.693147181f * (1.0f + 0x1p-20f), -e);
+    const float hi = __builtin_fmaf(l2, 0.693147181f * (1.0f - 0x1p-20f), e);
+    return {w ? lo : -0x1.fffffep+127f, w ? hi : __builtin_inff()};
+}
+
 // ---------------------------------------------------------- descriptors
 enum : int32_t { kErrOverflow = 1, kErrInitStuck = 2, kErrExactness = 4 };
 

@@ -96,6 +96,16 @@ __device__ __noinline__ bool slow_decide(const Inst& I, uint64_t T, uint32_t slo
     return accept_slow(delta, u53_of(draw(I.k0, I.k1, T, slot, kTagFlip)));
 }
 
+// The decision of decide_fast and accept_slow on the attempt's own draw: bit 0
+// accepted, bit 1 taken by the slow path.  For the attempts that the bounds of
+// bounds_of leave open.
+__device__ __noinline__ int decide_draw(const Inst& I, uint64_t T, uint32_t slot, double delta)
+{
+    const uint64_t u53 = u53_of(draw(I.k0, I.k1, T, slot, kTagFlip));
+    const int f = decide_fast(delta, threshold_of(u53, I.band), I.band);
+    return f == 2 ? 2 | (accept_slow(delta, u53) ? 1 : 0) : f;
+}
+
 // Native vectors for the draw chunks, loaded from the global address space
 // (plain vector loads rather than flat addressing).
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
@@ -429,9 +439,29 @@ __host__ __device__ inline size_t wave_lds_bytes(int model, int L, int WB, int G
     return s;
 }
 
-__device__ __forceinline__ uint32_t shfl32(uint32_t v, int src)
+// Lane (byte offset / 4)'s value of v.
+__device__ __forceinline__ double bperm_d(double v, int byte)
 {
-    return (uint32_t)__builtin_amdgcn_ds_bpermute(src << 2, (int)v);
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(byte, (int)(uint32_t)(u >> 32));
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(byte, (int)(uint32_t)u);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Index of the lowest set bit of a wave-uniform mask, 2^32 - 1 if there is none.
+__device__ __forceinline__ uint32_t first_bit(uint64_t m)
+{
+    uint32_t r;
+    asm("s_ff1_i32_b64 %0, %1" : "=s"(r) : "s"(m));
+    return r;
+}
+
+// Exact decision of one walker's attempt, taken by the whole wave alike.
+__device__ __forceinline__ bool wave_decide(const Inst& I, uint64_t T, uint32_t slot, double delta, int lane)
+{
+    const int f = __builtin_amdgcn_readfirstlane(decide_draw(I, T, slot, delta));
+    if ((f & 2) && lane == 0) atomicAdd((unsigned long long*)&I.ctr->slow, 1ull);
+    return f & 1;
 }
 
 // Bin change of flipping Ising spin (r, c): rows w (row r), wu (r-1), wd (r+1).
@@ -590,20 +620,49 @@ __device__ void sweep_wave(const Inst& I, const Tile& tile, char* smem)
     // written when the walker leaves the bin or the window is stored.
     double B = rld(gl, idx);
     const double laneinc = (double)lane * incv;
+    const float rL = 1.0f / (float)L;
+    const float band32 = (float)band;
+    const uint64_t lanebit = 1ull << lane;
 
     for (int64_t j0 = 0; j0 < X; j0 += 64) {
         const int n = (int)((X - j0) < 64 ? (X - j0) : 64);
+        const uint64_t live = n == 64 ? ~0ull : ((1ull << n) - 1);
         // ---- lanes: draws and sites of the chunk's attempts
         const u32x4 x = draw(I.k0, I.k1, T0 + (uint64_t)(j0 + lane), (uint32_t)slot, kTagFlip);
         const int site = (int)(((uint64_t)x.x * (uint32_t)N) >> 32);
-        const int rr = site / L, cc = site - rr * L;
-        const int ru = rr == 0 ? L - 1 : rr - 1, rd = rr == L - 1 ? 0 : rr + 1;
-        const int cl = cc == 0 ? L - 1 : cc - 1, cr = cc == L - 1 ? 0 : cc + 1;
-        const int s_up = ru * L + cc, s_dn = rd * L + cc, s_lf = rr * L + cl, s_rt = rr * L + cr;
+        int rr = (int)((float)site * rL);          // site / L, at most one off (as in k_rng)
+        int cc = site - (int)__umul24((uint32_t)rr, (uint32_t)L);
+        if (cc < 0) { --rr; cc += L; }
+        else if (cc >= L) { ++rr; cc -= L; }
+        const bool top = rr == 0, bottom = rr == L - 1;
+        const int ru = top ? L - 1 : rr - 1, rd = bottom ? 0 : rr + 1;
+        const int s_up = top ? site + (N - L) : site - L, s_dn = bottom ? site - (N - L) : site + L;
+        const int s_lf = cc == 0 ? site + (L - 1) : site - 1, s_rt = cc == L - 1 ? site - (L - 1) : site + 1;
         const uint32_t off = MODEL == 0 ? 0u : (uint32_t)(((uint64_t)x.y * qm1) >> 32);
-        int d;                            // bin change of this lane's attempt
-        uint32_t nv = 0;                  // Potts: proposed state
-        auto evaluate = [&]() {           // on the lattice as it stands
+        // bounds of the acceptance threshold less the lane's updates: with y = B minus
+        // ln g of the candidate bin, y > whi accepts and y < wlo rejects for certain.
+        // (The differences round by at most 2^-46, far inside the bounds' own margin.)
+        const Bound32 tb = bounds_of(x.z, x.w, band32);
+        const double whi = (double)tb.hi - laneinc, wlo = (double)tb.lo - laneinc;
+        // attempts of the chunk at this attempt's site or one of its neighbours.
+        // Neighbourhoods are symmetric, so the later ones among them (qm) are
+        // exactly the attempts whose evaluation a flip of this one makes out of
+        // date, and the earlier ones (pm) those whose flip makes this one out of
+        // date.  (Sites sharing a map entry only add attempts to either set.)
+        if (lane < n) atomicOr((unsigned long long*)&lmap[ent(site)], lanebit);
+        const uint64_t nbh = lmap[ent(site)] | lmap[ent(s_up)] | lmap[ent(s_dn)] | lmap[ent(s_lf)] |
+                             lmap[ent(s_rt)];
+        if (lane < n) lmap[ent(site)] = 0;
+        const uint64_t pm = nbh & (lanebit - 1);
+        const uint64_t qm = nbh & ~(lanebit | (lanebit - 1));
+        uint64_t* const fword = lrow + (WIDE ? rr * wpr + (cc >> 6) : rr);   // Ising: the flip's word
+        const uint64_t fbit = 1ull << (cc & 63);
+
+        // the chain: rounds from one evaluation of the lattice to the next
+        uint32_t i = 0;                   // first attempt of the round
+        for (;;) {
+            int d;                        // bin change of this lane's attempt
+            uint32_t nv = 0;              // Potts: proposed state
             if (MODEL == 0) {
                 d = ising_d_words(lrow, wpr, rr, ru, rd, cc, L);
             } else {
@@ -615,126 +674,76 @@ __device__ void sweep_wave(const Inst& I, const Tile& tile, char* smem)
                 const int nnew = (n0 == nv) + (n1 == nv) + (n2 == nv) + (n3 == nv);
                 d = nold - nnew;
             }
-        };
-        evaluate();
-        const double vbl = threshold_of(u53_of(x), band);
-        const double vbl2 = vbl - 2.0 * band;     // below it a reject is certain
-        // attempts of the chunk at this attempt's site or one of its neighbours.
-        // Neighbourhoods are symmetric, so the later ones among them (qm) are
-        // exactly the attempts whose evaluation a flip of this one makes out of
-        // date, and the earlier ones (pm) those whose flip makes this one out of
-        // date.  (Sites sharing a map entry only add attempts to either set.)
-        const uint64_t lanebit = 1ull << lane;
-        if (lane < n) atomicOr((unsigned long long*)&lmap[ent(site)], lanebit);
-        const uint64_t nbh = lmap[ent(site)] | lmap[ent(s_up)] | lmap[ent(s_dn)] | lmap[ent(s_lf)] |
-                             lmap[ent(s_rt)];
-        if (lane < n) lmap[ent(site)] = 0;
-        const uint64_t pm = nbh & (lanebit - 1);
-        const uint64_t qm = nbh & ~(lanebit | (lanebit - 1));
-        const uint64_t live = n == 64 ? ~0ull : ((1ull << n) - 1);
-        uint64_t* const fword = lrow + (WIDE ? rr * wpr + (cc >> 6) : rr);   // Ising: the flip's word
-        const uint64_t fbit = 1ull << (cc & 63);
-        // zall: moves within the bin (d = 0, always accepted); stale: attempts that
-        // are out of date by the time the chain reaches them -- an earlier d = 0
-        // move since the last evaluation lies in the neighbourhood (fixed at the
-        // evaluation), or an accepted move with d != 0 since then (added per move)
-        uint64_t zall, nzl, stale;
-        int d4;                           // byte offset of the candidate bin's lane from idx
-        auto classify = [&](int i0) {
-            d4 = d << 2;
-            zall = __builtin_amdgcn_ballot_w64(d == 0) & live;
-            nzl = ~zall & live;
-            stale = __builtin_amdgcn_ballot_w64((pm & zall & (~0ull << i0)) != 0) & live;
-        };
-        classify(0);
-
-        // flips decided but not yet applied to the lattice (d = 0 moves and
-        // accepted moves); they are applied together before the lattice is read
-        // again (a re-evaluation, the next chunk)
-        uint64_t pend = 0;
-        auto apply = [&]() {
-            if (pend) {
-                if (__builtin_amdgcn_inverse_ballot_w64(pend)) {
-                    if (MODEL == 0) atomicXor((unsigned long long*)fword, fbit);
-                    else llat[site] = (uint8_t)nv;
-                }
-                pend = 0;
-            }
-        };
-
-        // the run loop; it leaves at the end of the chunk, and to move the
-        // register window when a move brings the walker within four bins of its
-        // edge (then it continues at attempt i)
-        int i = 0;
-        for (;;) {
-            const uint64_t run = ~0ull << i;              // every mask below is within live
-            const double t = B + laneinc;                 // ln g of the bin, exact
-            const int pos4 = d4 + (idx << 2);
-            const double gp = __builtin_bit_cast(
-                double, ((uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(
-                             pos4, (int)(uint32_t)(__builtin_bit_cast(uint64_t, gl) >> 32))
-                         << 32) |
-                            (uint32_t)__builtin_amdgcn_ds_bpermute(pos4, (int)(uint32_t)__builtin_bit_cast(uint64_t, gl)));
-            const double dl = t - gp;                     // ln g now - ln g of the candidate, exact
-            const uint64_t gt = __builtin_amdgcn_ballot_w64(dl > vbl);
-            const uint64_t ge = __builtin_amdgcn_ballot_w64(dl >= vbl2);    // holds gt
-            const uint64_t nzr = nzl & run;               // attempts with d != 0 from i on
-            const uint64_t acc = gt & nzr;
-            const uint64_t stop = acc | (stale & run);
-            uint64_t sbit = stop & (~stop + 1);           // the first stop, or 0
-            uint64_t below = sbit - 1;                    // lanes below it (all if none)
-            // accepted and out of date counts as out of date: re-evaluated first
-            uint64_t mv = sbit & acc & ~stale;            // the accepted move, or 0
-            // attempts inside the guard band are decided exactly, in order
-            uint64_t amb = ge & ~gt & nzr & below;
-            if (__builtin_expect(amb != 0, 0)) {
-                do {
-                    const int kk = (int)__builtin_ctzll(amb);
-                    amb &= amb - 1;
-                    if (lane == 0) atomicAdd((unsigned long long*)&I.ctr->slow, 1ull);
-                    if (__builtin_amdgcn_readfirstlane(
-                            slow_decide(I, T0 + (uint64_t)j0 + (uint64_t)kk, (uint32_t)slot, rld(dl, kk)) ? 1 : 0)) {
-                        sbit = mv = 1ull << kk;
-                        below = sbit - 1;
-                        break;
+            const int d4 = d << 2;
+            // zall: moves within the bin (d = 0, always accepted); nzr: attempts with
+            // d != 0 not yet decided; stale: attempts that are out of date by the time
+            // the chain reaches them -- a d = 0 move of this round lies in the
+            // neighbourhood (fixed here), or an accepted move with d != 0 of the round
+            // does (added per move); none of them lies below the attempt reached
+            const uint64_t run = ~0ull << i;
+            const uint64_t zall = __builtin_amdgcn_ballot_w64(d == 0) & live & run;
+            uint64_t nzr = live & run & ~zall;
+            uint64_t stale = __builtin_amdgcn_ballot_w64((pm & zall) != 0) & live & run;
+            uint64_t moved = 0;           // accepted moves with d != 0 of the round
+            uint32_t js;
+            for (;;) {
+                const int pos4 = d4 + (idx << 2);
+                const double gp = bperm_d(gl, pos4);
+                const double y = B - gp;                      // exact
+                const uint64_t gt = __builtin_amdgcn_ballot_w64(y > whi);
+                const uint64_t ge = __builtin_amdgcn_ballot_w64(y >= wlo);    // holds gt
+                uint64_t acc = gt & nzr;
+                js = first_bit(stale);
+                if (__builtin_expect(gt != ge, 0)) {
+                    // attempts between the bounds are decided exactly, in order, up to
+                    // the first accepted or out-of-date one
+                    const uint64_t stop = acc | stale;
+                    uint64_t amb = ge & ~gt & nzr & ((stop & (~stop + 1)) - 1);
+                    while (amb) {
+                        const uint32_t kk = first_bit(amb);
+                        const double dl = rld(y, (int)kk) + (double)kk * incv;   // exact
+                        if (wave_decide(I, T0 + (uint64_t)j0 + (uint64_t)kk, (uint32_t)slot, dl, lane)) {
+                            acc = 1ull << kk;
+                            break;
+                        }
+                        amb &= amb - 1;
                     }
-                } while (amb);
-            }
-            // attempts i..js-1 were rejected or moved within the bin; the d = 0
-            // moves among them and an accepted move at js flip
-            pend |= (zall & run & below) | mv;
-            if (__builtin_expect(mv != 0, 1)) {
-                const int js = (int)__builtin_ctzll(mv);
-                // the old bin after attempts up to js - 1 is t at lane js; the
-                // differences below are exact (multiples of 2^-k, small)
-                const double tjs = rld(t, js);
-                const double jsinc = tjs - B;             // js incv
-                if (lane == idx) gl = tjs;
-                idx += __builtin_amdgcn_readlane(d, js);
-                stale |= rl64(qm, js);
-                // the new bin's entry lacks attempt js's update, so B = entry - js incv
-                B = rld(gl, idx) - jsinc;
-                i = js + 1;
+                }
+                // the first accepted move ends the step, unless an attempt at or before
+                // it is out of date
+                const uint32_t ja = first_bit(acc);
+                if (ja >= js) break;
+                // the old bin after attempts up to ja - 1 holds B + ja incv; the new
+                // bin's entry lacks attempt ja's update, so B = entry - ja incv (exact)
+                const double shift = rld(laneinc, (int)ja);
+                const double told = B + shift;
+                if (lane == idx) gl = told;
+                idx += __builtin_amdgcn_readlane(d, (int)ja);
+                B = rld(gl, idx) - shift;
+                stale |= rl64(qm, (int)ja);
+                nzr &= ~1ull << ja;
+                moved |= 1ull << ja;
                 if (__builtin_expect((unsigned)(idx - 4) > 55u, 0)) {   // idx < 4 or idx > 59
-                    // store the window with the bin's current value (B + i incv),
+                    // store the window with the bin's current value (B + (ja + 1) incv),
                     // reload it around the walker; the entry may stay current
-                    if (lane == idx) gl = B + (double)i * incv;
+                    if (lane == idx) gl = B + (double)(ja + 1) * incv;
                     store_window();
                     const int bb = b0 + idx;
                     b0 = bb - 32 < 0 ? 0 : (bb - 32 > b0max ? b0max : bb - 32);
                     idx = bb - b0;
                     load_window();
                 }
-                if (i >= n) break;
-            } else {
-                if (!stop) break;
-                i = (int)__builtin_ctzll(stop);           // attempt i is out of date
-                apply();
-                evaluate();
-                classify(i);
             }
+            // the round's flips: its d = 0 moves before the out-of-date attempt js (all
+            // of them if there is none) and its accepted moves
+            const uint64_t flips = (zall & (js < 64 ? (1ull << js) - 1 : ~0ull)) | moved;
+            if (__builtin_amdgcn_inverse_ballot_w64(flips)) {
+                if (MODEL == 0) atomicXor((unsigned long long*)fword, fbit);
+                else llat[site] = (uint8_t)nv;
+            }
+            if (js >= 64) break;
+            i = js;                       // evaluated again on the lattice as it stands now
         }
-        apply();
         B += (double)n * incv;
     }
     if (lane == idx) gl = B;
