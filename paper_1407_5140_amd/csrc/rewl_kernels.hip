@@ -125,6 +125,10 @@ __device__ __forceinline__ uint64_t rl64(uint64_t v, int l)
 {
     return ((uint64_t)rl((uint32_t)(v >> 32), l) << 32) | rl((uint32_t)v, l);
 }
+__device__ __forceinline__ float rlf(float v, int l)
+{
+    return __builtin_bit_cast(float, rl(__builtin_bit_cast(uint32_t, v), l));
+}
 __device__ __forceinline__ double rld(double v, int l)
 {
     return __builtin_bit_cast(double, rl64(__builtin_bit_cast(uint64_t, v), l));
@@ -440,12 +444,9 @@ __host__ __device__ inline size_t wave_lds_bytes(int model, int L, int WB, int G
 }
 
 // Lane (byte offset / 4)'s value of v.
-__device__ __forceinline__ double bperm_d(double v, int byte)
+__device__ __forceinline__ float bperm_f(float v, int byte)
 {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(byte, (int)(uint32_t)(u >> 32));
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(byte, (int)(uint32_t)u);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+    return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(byte, __builtin_bit_cast(int, v)));
 }
 
 // Index of the lowest set bit of a wave-uniform mask, 2^32 - 1 if there is none.
@@ -455,6 +456,25 @@ __device__ __forceinline__ uint32_t first_bit(uint64_t m)
     asm("s_ff1_i32_b64 %0, %1" : "=s"(r) : "s"(m));
     return r;
 }
+
+// c if the wave-uniform masks a and b are equal, else 0 (kept on the scalar side).
+__device__ __forceinline__ uint64_t equal_then(uint64_t a, uint64_t b, uint64_t c)
+{
+    uint64_t r;
+    asm("s_cmp_eq_u64 %1, %2\n\ts_cselect_b64 %0, %3, 0" : "=s"(r) : "s"(a), "s"(b), "s"(c) : "scc");
+    return r;
+}
+
+// c if bit i of the wave-uniform mask m is set, else 0.
+__device__ __forceinline__ uint64_t bit_then(uint64_t m, int i, uint64_t c)
+{
+    uint64_t r;
+    asm("s_bitcmp1_b64 %1, %2\n\ts_cselect_b64 %0, %3, 0" : "=s"(r) : "s"(m), "s"(i), "s"(c) : "scc");
+    return r;
+}
+
+// Bit i of a wave-uniform mask set.
+__device__ __forceinline__ void set_bit(uint64_t& m, uint32_t i) { asm("s_bitset1_b64 %0, %1" : "+s"(m) : "s"(i)); }
 
 // Exact decision of one walker's attempt, taken by the whole wave alike.
 __device__ __forceinline__ bool wave_decide(const Inst& I, uint64_t T, uint32_t slot, double delta, int lane)
@@ -614,14 +634,39 @@ __device__ void sweep_wave(const Inst& I, const Tile& tile, char* smem)
         }
     };
     load_window();
-    // B + j incv is the walker's ln g at its current bin before attempt j of the
-    // chunk.  The register window's entry for that bin is left stale while the
-    // walker stays there (only attempts with d != 0 read the window) and is
-    // written when the walker leaves the bin or the window is stored.
-    double B = rld(gl, idx);
-    const double laneinc = (double)lane * incv;
+    // The steps compare in FP32: g0 = ln g of each bin of the window less that of
+    // the bin the walker was in when it was taken, gl holding the exact values of
+    // that moment; cnt = visits since then of the bins that the walker has left,
+    // cur = g0 + cnt 2^-k.  The walker came to its bin at attempt je of the chunk,
+    // and lb + j 2^-k is its ln g there before attempt j.  The walker may step to
+    // the bins of `safe`, whose g0 is below 64, away from the window's edge; when it
+    // leaves them, and at the end of a chunk, the visits go into gl (exact) and g0 is
+    // taken afresh.  Every quantity that a decision can depend on then stays below
+    // 512, the seven roundings on its way (six of at most 2^-16) below kErr32, and an
+    // attempt closer to its threshold than that is decided on the exact values.
+    constexpr float kErr32 = 0x1p-13f;
+    const float inc32 = (float)incv, laneinc = (float)lane * inc32;       // exact
+    float g0, cur, cnt = 0.0f, je = 0.0f, lb;
+    uint64_t safe;
+    auto settle = [&](int j) {            // attempts below j of the chunk are decided
+        cnt += lane == idx ? (float)j - je : 0.0f;
+        gl = __builtin_fma((double)cnt, incv, gl);            // exact
+        cnt = 0.0f;
+        if (__builtin_expect((unsigned)(idx - 4) > 55u, 0)) { // idx < 4 or idx > 59
+            store_window();                                   // move the window around the walker
+            const int bb = b0 + idx;
+            b0 = bb - 32 < 0 ? 0 : (bb - 32 > b0max ? b0max : bb - 32);
+            idx = bb - b0;
+            load_window();
+        }
+        cur = g0 = (float)(gl - rld(gl, idx));
+        safe = __builtin_amdgcn_ballot_w64(__builtin_fabsf(g0) < 64.0f) & 0x0ffffffffffffff0ull;
+        je = (float)j;
+        lb = -je * inc32;
+    };
+    settle(0);
     const float rL = 1.0f / (float)L;
-    const float band32 = (float)band;
+    const float band32 = (float)band + kErr32;
     const uint64_t lanebit = 1ull << lane;
 
     for (int64_t j0 = 0; j0 < X; j0 += 64) {
@@ -639,11 +684,10 @@ __device__ void sweep_wave(const Inst& I, const Tile& tile, char* smem)
         const int s_up = top ? site + (N - L) : site - L, s_dn = bottom ? site - (N - L) : site + L;
         const int s_lf = cc == 0 ? site + (L - 1) : site - 1, s_rt = cc == L - 1 ? site - (L - 1) : site + 1;
         const uint32_t off = MODEL == 0 ? 0u : (uint32_t)(((uint64_t)x.y * qm1) >> 32);
-        // bounds of the acceptance threshold less the lane's updates: with y = B minus
-        // ln g of the candidate bin, y > whi accepts and y < wlo rejects for certain.
-        // (The differences round by at most 2^-46, far inside the bounds' own margin.)
+        // bounds of the acceptance threshold less the lane's updates: with y = lb minus
+        // cur of the candidate bin, y > whi accepts and y < wlo rejects for certain
         const Bound32 tb = bounds_of(x.z, x.w, band32);
-        const double whi = (double)tb.hi - laneinc, wlo = (double)tb.lo - laneinc;
+        const float whi = tb.hi - laneinc, wlo = tb.lo - laneinc;
         // attempts of the chunk at this attempt's site or one of its neighbours.
         // Neighbourhoods are symmetric, so the later ones among them (qm) are
         // exactly the attempts whose evaluation a flip of this one makes out of
@@ -657,6 +701,10 @@ __device__ void sweep_wave(const Inst& I, const Tile& tile, char* smem)
         const uint64_t qm = nbh & ~(lanebit | (lanebit - 1));
         uint64_t* const fword = lrow + (WIDE ? rr * wpr + (cc >> 6) : rr);   // Ising: the flip's word
         const uint64_t fbit = 1ull << (cc & 63);
+
+        // 64 less the index of the first attempt that this one's flip makes out of date
+        // (0: there is none), in the upper half of the word that a step reads of its move
+        const int cut = (64 - (int)__builtin_popcountll((qm - 1) & ~qm)) << 16;
 
         // the chain: rounds from one evaluation of the lattice to the next
         uint32_t i = 0;                   // first attempt of the round
@@ -674,79 +722,105 @@ __device__ void sweep_wave(const Inst& I, const Tile& tile, char* smem)
                 const int nnew = (n0 == nv) + (n1 == nv) + (n2 == nv) + (n3 == nv);
                 d = nold - nnew;
             }
-            const int d4 = d << 2;
-            // zall: moves within the bin (d = 0, always accepted); nzr: attempts with
-            // d != 0 not yet decided; stale: attempts that are out of date by the time
-            // the chain reaches them -- a d = 0 move of this round lies in the
-            // neighbourhood (fixed here), or an accepted move with d != 0 of the round
-            // does (added per move); none of them lies below the attempt reached
-            const uint64_t run = ~0ull << i;
-            const uint64_t zall = __builtin_amdgcn_ballot_w64(d == 0) & live & run;
-            uint64_t nzr = live & run & ~zall;
-            uint64_t stale = __builtin_amdgcn_ballot_w64((pm & zall) != 0) & live & run;
+            const int d4 = d << 2, word = cut + d4;
+            // zall: moves within the bin (d = 0, always accepted); stale: attempts with
+            // one of them in the neighbourhood; drop: how many attempts the first that is
+            // out of date, as far as the moves made go, cuts off the chunk's 64; open:
+            // the attempts before it with d != 0 that are not yet decided
+            const uint64_t run = live & (~0ull << i);
+            const uint64_t zall = __builtin_amdgcn_ballot_w64(d == 0) & run;
+            const uint64_t stale = __builtin_amdgcn_ballot_w64((pm & zall) != 0) & run;
+            const uint64_t nz = run & ~zall;
+            uint64_t open = nz & (stale - 1) & ~stale;
+            int drop = 64 - (int)__builtin_popcountll((stale - 1) & ~stale);
             uint64_t moved = 0;           // accepted moves with d != 0 of the round
-            uint32_t js;
             for (;;) {
-                const int pos4 = d4 + (idx << 2);
-                const double gp = bperm_d(gl, pos4);
-                const double y = B - gp;                      // exact
-                const uint64_t gt = __builtin_amdgcn_ballot_w64(y > whi);
-                const uint64_t ge = __builtin_amdgcn_ballot_w64(y >= wlo);    // holds gt
-                uint64_t acc = gt & nzr;
-                js = first_bit(stale);
-                if (__builtin_expect(gt != ge, 0)) {
-                    // attempts between the bounds are decided exactly, in order, up to
-                    // the first accepted or out-of-date one
-                    const uint64_t stop = acc | stale;
-                    uint64_t amb = ge & ~gt & nzr & ((stop & (~stop + 1)) - 1);
-                    while (amb) {
-                        const uint32_t kk = first_bit(amb);
-                        const double dl = rld(y, (int)kk) + (double)kk * incv;   // exact
-                        if (wave_decide(I, T0 + (uint64_t)j0 + (uint64_t)kk, (uint32_t)slot, dl, lane)) {
-                            acc = 1ull << kk;
-                            break;
-                        }
-                        amb &= amb - 1;
+                // Steps from one accepted move with d != 0 to the next.  A step is one
+                // dependent chain (look up, compare, first accepted, its bin change) whose
+                // instructions a wave alone on its SIMD issues one by one (4.5 cycles for
+                // most, 6 in FP64, 11 for v_readlane, 24 for a branch): so there is one
+                // branch, the next step's lookup is issued before this one is known to be a
+                // move, and the bookkeeping runs while it is under way.
+                uint64_t gt, ge, next = bit_then(safe, idx, open);
+                uint32_t ja;
+                int to;
+                float jf, gn, gp = bperm_f(cur, d4 + (idx << 2));
+                auto step = [&]() {
+                    const float y = lb - gp;
+                    gt = __builtin_amdgcn_ballot_w64(y > whi);
+                    ge = __builtin_amdgcn_ballot_w64(y >= wlo);       // holds gt
+                    const uint64_t acc = gt & next;
+                    ja = first_bit(acc);
+                    jf = (float)(int)ja;
+                    cnt += lane == idx ? jf - je : 0.0f;              // the old bin's visits
+                    cur = __builtin_fmaf(cnt, inc32, g0);
+                    gn = rlf(gp, (int)ja);                            // the new bin's entry
+                    to = (idx << 2) + __builtin_amdgcn_readlane(word, (int)ja);
+                    gp = bperm_f(cur, d4 + to);                       // lane: bits 2 to 7
+                    __builtin_amdgcn_sched_barrier(0);
+                    // no move, or some attempt between the bounds: left to the code below
+                    return equal_then(gt, ge, acc) != 0;
+                };
+                auto move = [&]() {
+                    idx = (to >> 2) & 63;
+                    je = jf;
+                    lb = __builtin_fmaf(-jf, inc32, gn);
+                    drop = max(drop, to >> 16);
+                    open = nz & (~0ull >> drop) & (~1ull << ja);
+                    set_bit(moved, ja);
+                };
+                bool go = step();
+                while (go) {
+                    move();
+                    next = bit_then(safe, idx, open);
+                    __builtin_amdgcn_sched_barrier(0);
+                    go = step();
+                }
+                cnt -= lane == idx ? jf - je : 0.0f;                  // the step not taken
+                cur = __builtin_fmaf(cnt, inc32, g0);
+                // the usual end of a round: nothing accepted, nothing between the bounds
+                if (equal_then(gt, ge, bit_then(safe, idx, 1)) != 0) break;
+                if (!((safe >> idx) & 1)) {
+                    settle(64 - (int)__builtin_clzll(moved));         // up to the last move
+                    continue;
+                }
+                // attempts between the bounds are decided exactly, in order, up to the
+                // first accepted one
+                uint64_t acc = gt & open, amb = ge & ~gt & open & (acc - 1) & ~acc;
+                if (__builtin_expect((acc | amb) == 0, 1)) break;
+                while (amb) {
+                    const uint32_t kk = first_bit(amb);
+                    const int cand = idx + __builtin_amdgcn_readlane(d, (int)kk);
+                    const double here = __builtin_fma((double)(rlf(cnt, idx) + ((float)kk - je)), incv, rld(gl, idx));
+                    const double there = __builtin_fma((double)rlf(cnt, cand), incv, rld(gl, cand));
+                    if (wave_decide(I, T0 + (uint64_t)j0 + (uint64_t)kk, (uint32_t)slot, here - there, lane)) {
+                        acc = 1ull << kk;
+                        break;
                     }
+                    amb &= amb - 1;
                 }
-                // the first accepted move ends the step, unless an attempt at or before
-                // it is out of date
-                const uint32_t ja = first_bit(acc);
-                if (ja >= js) break;
-                // the old bin after attempts up to ja - 1 holds B + ja incv; the new
-                // bin's entry lacks attempt ja's update, so B = entry - ja incv (exact)
-                const double shift = rld(laneinc, (int)ja);
-                const double told = B + shift;
-                if (lane == idx) gl = told;
-                idx += __builtin_amdgcn_readlane(d, (int)ja);
-                B = rld(gl, idx) - shift;
-                stale |= rl64(qm, (int)ja);
-                nzr &= ~1ull << ja;
-                moved |= 1ull << ja;
-                if (__builtin_expect((unsigned)(idx - 4) > 55u, 0)) {   // idx < 4 or idx > 59
-                    // store the window with the bin's current value (B + (ja + 1) incv),
-                    // reload it around the walker; the entry may stay current
-                    if (lane == idx) gl = B + (double)(ja + 1) * incv;
-                    store_window();
-                    const int bb = b0 + idx;
-                    b0 = bb - 32 < 0 ? 0 : (bb - 32 > b0max ? b0max : bb - 32);
-                    idx = bb - b0;
-                    load_window();
-                }
+                if (!acc) break;
+                ja = first_bit(acc);
+                jf = (float)(int)ja;
+                cnt += lane == idx ? jf - je : 0.0f;
+                cur = __builtin_fmaf(cnt, inc32, g0);
+                gn = rlf(cur, idx + __builtin_amdgcn_readlane(d, (int)ja));
+                to = (idx << 2) + __builtin_amdgcn_readlane(word, (int)ja);
+                move();
             }
-            // the round's flips: its d = 0 moves before the out-of-date attempt js (all
-            // of them if there is none) and its accepted moves
-            const uint64_t flips = (zall & (js < 64 ? (1ull << js) - 1 : ~0ull)) | moved;
+            // the round's flips: its accepted moves, and its d = 0 moves before the first
+            // out-of-date attempt
+            const uint64_t flips = (zall & (~0ull >> drop)) | moved;
             if (__builtin_amdgcn_inverse_ballot_w64(flips)) {
                 if (MODEL == 0) atomicXor((unsigned long long*)fword, fbit);
                 else llat[site] = (uint8_t)nv;
             }
-            if (js >= 64) break;
-            i = js;                       // evaluated again on the lattice as it stands now
+            i = 64 - drop;
+            if (i >= (uint32_t)n) break;  // else evaluated again on the lattice as it stands now
         }
-        B += (double)n * incv;
+        settle(n);
+        je = lb = 0.0f;
     }
-    if (lane == idx) gl = B;
     store_window();
 
     // ---- write back (HG: the window's store above is the write back)
