@@ -48,6 +48,17 @@ __device__ __forceinline__ float gelu_grad(float a)
            a * 0.39894228040143268f * expf(-0.5f * a * a);
 }
 
+// Index of the minibatch row that batch row r of a step takes: floor(u n) of a fixed
+// hash (splitmix64 of (seed, step, r); only the sample order depends on it).
+__device__ __forceinline__ int pick_row(uint64_t step, uint32_t seed, int r, int n)
+{
+    uint64_t z = ((uint64_t)seed << 32) ^ (step * 0x9E3779B97F4A7C15ull) ^ (uint64_t)r * 0xD1B54A32D192ED03ull;
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    z ^= z >> 31;
+    return (int)(((z >> 32) * (uint64_t)n) >> 32);
+}
+
 // ---------------------------------------------------------------- GEMM
 // C = op(A) op(B) on the matrix cores: A(i,k) = A[i*lda + k] (ta = 0) or
 // A[k*lda + i] (ta = 1); B(k,j) = B[k*ldb + j] (tb = 0) or B[j*ldb + k] (tb = 1);
@@ -289,14 +300,395 @@ __global__ void k_gather(const float* __restrict__ X, const float* __restrict__ 
 {
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= B) return;
-    // splitmix64 of (seed, step, r): any fixed hash serves, only the sample order depends on it
-    uint64_t z = ((uint64_t)seed << 32) ^ (step * 0x9E3779B97F4A7C15ull) ^ (uint64_t)r * 0xD1B54A32D192ED03ull;
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-    z ^= z >> 31;
-    const int k = (int)(((z >> 32) * (uint64_t)n) >> 32);
+    const int k = pick_row(step, seed, r, n);
     for (int i = 0; i < in_dim; ++i) xb[r * in_dim + i] = X[(size_t)k * in_dim + i];
     yb[r] = Y[k];
+}
+
+// ------------------------------------------------------------- fused pass
+// The whole network on one block per 16 rows: the activations of a layer (and on
+// the way back its errors) stay in LDS, so a step is two launches (k_net and
+// k_grad: 23.5 + 9.6 us for 4 096 rows of 256 units and 3 layers) instead of 29
+// (181 us) and nothing but what the weight gradients need goes to memory.  Every
+// sum keeps the order it had layer by layer (batches up to 16 384 rows).  A block of up to 8 waves takes one column tile of 32 per wave
+// and round; 16 rows rather than 32 fill only half of the 32 x 32 x 16 tile's
+// rows, but give 4 096 rows 256 blocks, and the pass is bound by latency and by
+// the erf and exp of its elements, not by the matrix cores.
+// Operands are kept in the order in which a lane takes them, so every load is a
+// coalesced 1 KB: a "fragment" of 32 columns and 16 k holds, for lane l, column
+// l % 32 and k = 8 (l / 32) .. + 7; fragment (column tile c, k block b) of a matrix
+// with KB k blocks starts at (c KB + b) 512.
+constexpr int kRows = 16, kPadH = 8;          // LDS rows of H + 8 elements spread the banks
+// Units up to which a step is faster this way (us per step, layer by layer -> fused; 3 layers):
+// 64 units 157 -> 28, 256: 181 -> 37, 512: 250 -> 75, 1024: 454 -> 211, all of 4 096 rows; of
+// 64 rows 256 units 131 -> 27, of 256 rows 1024 units 212 -> 136, but 2048 units 359 -> 414.
+constexpr int kFusedMaxH = 1024;
+
+__host__ __device__ inline size_t frag_pos(int col, int k, int KB)
+{
+    return ((size_t)((col >> 5) * KB + (k >> 4)) * 64 + ((k >> 3) & 1) * 32 + (col & 31)) * 8 + (k & 7);
+}
+// offsets of layer l's matrix and bias in the flat parameter vector, and behind them
+__host__ __device__ inline int off_weight(int in, int H, int l) { return l == 0 ? 0 : in * H + H + (l - 1) * (H * H + H); }
+__host__ __device__ inline int off_bias(int in, int H, int l) { return off_weight(in, H, l) + (l == 0 ? in * H : H * H); }
+// floats that a block adds to the gradient on its own: W1, the biases, w_out, b_out, loss
+__host__ __device__ inline int part_size(int in, int H, int nl) { return (in + nl + 1) * H + 2; }
+
+struct NetArgs {
+    const float* p;          // flat parameters
+    const __bf16 *wf, *wb;   // [nl - 1][H H]: fragments of the forward product (columns: units)
+                             // and of the backward one (columns: inputs)
+    const float *X, *T;      // rows and targets; gather: the data set
+    int in, H, nl, nvalid, nb;   // nb blocks of 16 rows; rows from nvalid on count as zero
+    int gather;              // 0, or the number of rows to draw from
+    uint32_t seed;
+    uint64_t step;
+    float* y;                // outputs (inference)
+    float* dg;               // gelu' of every element, as the threads hold them
+    __bf16 *actf, *df;       // activations of layers 0 .. nl - 2, errors of layers 1 .. nl - 1,
+                             // [nl - 1][16 nb H]: fragments with k = rows
+    float* part;             // [nb][part_size]
+};
+
+// acc = src . fragments of column tile t (src: LDS rows, K = H), k ascending
+template <int CH>
+__device__ __forceinline__ f32x16 tile_product(const __bf16* src, const __bf16* __restrict__ w, int t, int H,
+                                               int lane)
+{
+    const int KB = H >> 4;
+    const bf16x8* B = (const bf16x8*)w + (size_t)t * KB * 64 + lane;
+    const __bf16* a = src + (lane & 15) * (H + kPadH) + (lane >> 5) * 8;
+    f32x16 acc = {};
+    bf16x8 cur[CH], nxt[CH];
+#pragma unroll
+    for (int u = 0; u < CH; ++u) cur[u] = B[u * 64];
+    for (int b = 0; b < KB; b += CH) {
+        if (b + CH < KB) {
+#pragma unroll
+            for (int u = 0; u < CH; ++u) nxt[u] = B[(b + CH + u) * 64];
+        }
+#pragma unroll
+        for (int u = 0; u < CH; ++u)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(a + (b + u) * 16), cur[u], acc, 0, 0, 0);
+#pragma unroll
+        for (int u = 0; u < CH; ++u) cur[u] = nxt[u];
+    }
+    return acc;
+}
+__device__ __forceinline__ f32x16 tile_product(const __bf16* src, const __bf16* w, int t, int H, int lane)
+{
+    return (H & 127) == 0 ? tile_product<8>(src, w, t, H, lane) : tile_product<4>(src, w, t, H, lane);
+}
+
+// the 8 elements of a thread: row_of(r, half), r = 0 .. 7, of one column
+__device__ __forceinline__ int row_of(int r, int half) { return 8 * (r >> 2) + 4 * half + (r & 3); }
+
+// sum of a column's 16 rows in row order, held by the lanes of half 1
+__device__ __forceinline__ float row_sum(const float (&v)[8], int half)
+{
+    float s = 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {                 // rows 4 q .. 4 q + 3 lie with half q & 1
+        if (half == (q & 1))
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s += v[4 * (q >> 1) + r];
+        if (q < 3) {
+            const float o = __shfl_xor(s, 32);
+            if (half != (q & 1)) s = o;
+        }
+    }
+    return s;
+}
+
+// 4 rows each of v as two 8-byte stores into the fragments of k block kb
+__device__ __forceinline__ void store_frag(__bf16* f, int t, int kb, int nb, int lane, const __bf16 (&v)[8])
+{
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    __bf16* q = f + ((size_t)(t * nb + kb) * 64 + (lane & 31)) * 8 + (lane >> 5) * 4;
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        __bf16 w[4] = {v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+        *(u32x2*)(q + g * 32 * 8) = __builtin_bit_cast(u32x2, w);
+    }
+}
+
+template <bool TRAIN>
+__global__ void __launch_bounds__(512) k_net(const NetArgs A)
+{
+    extern __shared__ __align__(16) char smem[];
+    __shared__ float xs[kRows * 16], ys[kRows], dys[kRows], ls[kRows];
+    const int H = A.H, in = A.in, nl = A.nl, T = H >> 5, ld = H + kPadH;
+    __bf16* src = (__bf16*)smem;
+    __bf16* dst = src + kRows * ld;
+    const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, wave = tid >> 6, nw = nthr >> 6;
+    const int half = lane >> 5, kb = blockIdx.x, r0 = kb * kRows;
+    const size_t HH = (size_t)H * H, BH = (size_t)A.nb * kRows * H;
+
+    for (int e = tid; e < kRows * in; e += nthr) {
+        const int r = e / in, row = r0 + r;
+        const int k = A.gather ? pick_row(A.step, A.seed, row, A.gather) : row;
+        xs[e] = row < A.nvalid ? A.X[(size_t)k * in + (e - r * in)] : 0.f;
+    }
+    __syncthreads();
+
+    // the element function of layer l on column tile t: activations to LDS
+    auto epilogue = [&](int l, int t, const float (&s)[8]) {
+        const int j = 32 * t + (lane & 31);
+        __bf16 a16[8];
+        float dgv[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const float a = s[r], e = 1.0f + erff(a * 0.70710678118654752f);
+            a16[r] = (__bf16)(0.5f * a * e);
+            if (TRAIN) dgv[r] = 0.5f * e + a * 0.39894228040143268f * expf(-0.5f * a * a);
+            dst[row_of(r, half) * ld + j] = a16[r];
+        }
+        if (TRAIN) {
+            float4* q = (float4*)(A.dg + l * BH) + ((size_t)kb * T + t) * 128 + lane;
+            q[0] = make_float4(dgv[0], dgv[1], dgv[2], dgv[3]);
+            q[64] = make_float4(dgv[4], dgv[5], dgv[6], dgv[7]);
+            if (l < nl - 1) store_frag(A.actf + l * BH, t, kb, A.nb, lane, a16);
+        }
+    };
+    auto flip = [&]() {
+        __syncthreads();
+        __bf16* x = src;
+        src = dst;
+        dst = x;
+    };
+
+    // ---- forward
+    for (int t = wave; t < T; t += nw) {
+        const int j = 32 * t + (lane & 31);
+        float s[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) s[r] = A.p[in * H + j];
+        for (int i = 0; i < in; ++i) {
+            const float w = A.p[i * H + j];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) s[r] += xs[row_of(r, half) * in + i] * w;
+        }
+        epilogue(0, t, s);
+    }
+    flip();
+    for (int l = 1; l < nl; ++l) {
+        for (int t = wave; t < T; t += nw) {
+            const f32x16 acc = tile_product(src, A.wf + (l - 1) * HH, t, H, lane);
+            const float b = A.p[off_bias(in, H, l) + 32 * t + (lane & 31)];
+            float s[8];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) s[r] = acc[r] + b;
+            epilogue(l, t, s);
+        }
+        flip();
+    }
+    const float* wout = A.p + off_weight(in, H, nl);
+    for (int r = wave; r < kRows; r += nw) {
+        float s = 0.f;
+        for (int j = lane; j < H; j += 64) s += (float)src[r * ld + j] * wout[j];
+        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+        if (lane == 0) {
+            const float y = s + wout[H];
+            ys[r] = y;
+            if (!TRAIN && r0 + r < A.nvalid) A.y[r0 + r] = y;
+        }
+    }
+    if (!TRAIN) return;
+    __syncthreads();
+
+    // ---- loss and its derivative, gradient of the output layer
+    float* part = A.part + (size_t)kb * part_size(in, H, nl);
+    if (tid < kRows) {
+        const int row = r0 + tid;
+        float d = 0.f, l2 = 0.f;
+        if (row < A.nvalid) {
+            const int k = A.gather ? pick_row(A.step, A.seed, row, A.gather) : row;
+            d = ys[tid] - A.T[k];
+            l2 = d * d / (float)A.nvalid;
+            d = 2.f * d / (float)A.nvalid;
+        }
+        dys[tid] = d;
+        ls[tid] = l2;
+    }
+    __syncthreads();
+    float* pout = part + (in + nl) * H;
+    if (tid == 0) {
+        float s = 0.f, l2 = 0.f;
+        for (int r = 0; r < kRows; ++r) {
+            s += dys[r];
+            l2 += ls[r];
+        }
+        pout[H] = s;
+        pout[H + 1] = l2;
+    }
+    for (int j = tid; j < H; j += nthr) {
+        float s = 0.f;
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) s += dys[r] * (float)src[r * ld + j];
+        pout[j] = s;
+    }
+
+    // ---- backward: the error of layer l, from its own tile's sums v before gelu'
+    auto error = [&](int l, int t, const float (&v)[8]) {
+        const int j = 32 * t + (lane & 31);
+        const float4* q = (const float4*)(A.dg + l * BH) + ((size_t)kb * T + t) * 128 + lane;
+        const float4 g0 = q[0], g1 = q[64];
+        const float g[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+        float d[8];
+        __bf16 d16[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            d[r] = v[r] * g[r];
+            d16[r] = (__bf16)d[r];
+        }
+        const float cs = row_sum(d, half);
+        if (half) part[(in + l) * H + j] = cs;
+        if (l == 0) {
+            for (int i = 0; i < in; ++i) {
+                float x[8];
+#pragma unroll
+                for (int r = 0; r < 8; ++r) x[r] = xs[row_of(r, half) * in + i] * d[r];
+                const float s = row_sum(x, half);
+                if (half) part[i * H + j] = s;
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) dst[row_of(r, half) * ld + j] = d16[r];
+            store_frag(A.df + (l - 1) * BH, t, kb, A.nb, lane, d16);
+        }
+    };
+    for (int t = wave; t < T; t += nw) {
+        const float w = wout[32 * t + (lane & 31)];
+        float v[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) v[r] = dys[row_of(r, half)] * w;
+        error(nl - 1, t, v);
+    }
+    for (int l = nl - 1; l >= 1; --l) {
+        flip();
+        for (int t = wave; t < T; t += nw) {
+            const f32x16 acc = tile_product(src, A.wb + (l - 1) * HH, t, H, lane);
+            float v[8];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) v[r] = acc[r];
+            error(l - 1, t, v);
+        }
+    }
+}
+
+// Adam (Kingma & Ba) on one FP32 parameter
+struct AdamArgs {
+    float *m, *v;
+    float lr, b1, b2, eps, c1, c2;
+};
+__device__ __forceinline__ float adam_step(const AdamArgs& a, float p, float gi, int i)
+{
+    const float mi = a.b1 * a.m[i] + (1.f - a.b1) * gi;
+    const float vi = a.b2 * a.v[i] + (1.f - a.b2) * gi * gi;
+    a.m[i] = mi;
+    a.v[i] = vi;
+    return p - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+}
+
+// The gradient, and with ADAM the step on it.  Blocks 0 .. nm - 1: one 32 x 32 tile of a
+// hidden matrix's gradient act_{l-1}^T d_l each; wave z takes the z-th of S spans of `span`
+// row blocks, k ascending, and the spans are added in LDS in their order.  The other
+// blocks: 16 entries each of the row blocks' own sums, over 16 threads per entry.  Every
+// sum has a fixed order, and nothing is read back that was not needed anyway.
+template <bool ADAM>
+__global__ void __launch_bounds__(1024) k_grad(float* __restrict__ p, float* __restrict__ g, __bf16* __restrict__ wf,
+                                               __bf16* __restrict__ wb, const __bf16* __restrict__ actf,
+                                               const __bf16* __restrict__ df, int S, int span,
+                                               const float* __restrict__ part, int nb, int in, int H, int nl,
+                                               float* __restrict__ loss, AdamArgs ad)
+{
+    extern __shared__ __align__(16) char smem[];
+    float* sum = (float*)smem;                       // [S][32 x 32], or [16][17]
+    const int n32 = H >> 5, nm = (nl - 1) * n32 * n32, t = threadIdx.x;
+    if ((int)blockIdx.x < nm) {
+        const int l = blockIdx.x / (n32 * n32), q = blockIdx.x - l * n32 * n32, ti = q / n32, tj = q - ti * n32;
+        const int lane = t & 63, wave = t >> 6;
+        if (wave < S) {
+            const size_t BH = (size_t)nb * kRows * H;
+            const bf16x8* a = (const bf16x8*)(actf + l * BH) + (size_t)ti * nb * 64 + lane;
+            const bf16x8* b = (const bf16x8*)(df + l * BH) + (size_t)tj * nb * 64 + lane;
+            const int k0 = wave * span, k1 = k0 + span < nb ? k0 + span : nb;
+            f32x16 acc = {};
+            int k = k0;
+            for (; k + 8 <= k1; k += 8) {
+                bf16x8 av[8], bv[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    av[u] = a[(size_t)(k + u) * 64];
+                    bv[u] = b[(size_t)(k + u) * 64];
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[u], bv[u], acc, 0, 0, 0);
+            }
+            for (; k < k1; ++k)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[(size_t)k * 64], b[(size_t)k * 64], acc, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                sum[wave * 1024 + (8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * 32 + (lane & 31)] = acc[r];
+        }
+        __syncthreads();
+        const int off = off_weight(in, H, l + 1);
+        const size_t HH = (size_t)H * H;
+        for (int e = t; e < 1024; e += blockDim.x) {
+            float s = 0.f;
+            for (int z = 0; z < S; ++z) s += sum[z * 1024 + e];
+            const int i = 32 * ti + (e >> 5), j = 32 * tj + (e & 31), o = off + i * H + j;
+            if (ADAM) {
+                const float w = adam_step(ad, p[o], s, o);
+                p[o] = w;
+                wf[l * HH + frag_pos(j, i, H >> 4)] = (__bf16)w;
+                wb[l * HH + frag_pos(i, j, H >> 4)] = (__bf16)w;
+            } else {
+                g[o] = s;
+            }
+        }
+        return;
+    }
+    const int PS = part_size(in, H, nl), c = t & 15, gr = t >> 4, e = ((int)blockIdx.x - nm) * 16 + c;
+    float s = 0.f;
+    if (gr < 16) {
+        if (e < PS)
+            for (int z = gr; z < nb; z += 16) s += part[(size_t)z * PS + e];
+        sum[gr * 17 + c] = s;
+    }
+    __syncthreads();
+    for (int w = 8; w > 0; w >>= 1) {
+        if (gr < w) sum[gr * 17 + c] += sum[(gr + w) * 17 + c];
+        __syncthreads();
+    }
+    if (gr != 0 || e >= PS) return;
+    s = sum[c];
+    int i;
+    if (e < in * H) i = e;
+    else if (e < (in + nl) * H) {
+        const int l = e / H - in;
+        i = off_bias(in, H, l) + (e - (in + l) * H);
+    } else {
+        i = off_weight(in, H, nl) + (e - (in + nl) * H);      // w_out, b_out, then the loss
+        if (e == PS - 1) {
+            *loss = s;
+            return;
+        }
+    }
+    if (ADAM) p[i] = adam_step(ad, p[i], s, i);
+    else g[i] = s;
+}
+
+// both fragment copies of the hidden matrices, from the FP32 parameters
+__global__ void k_pack(const float* __restrict__ p, int in, int H, __bf16* __restrict__ wf, __bf16* __restrict__ wb)
+{
+    const int e = blockIdx.x * blockDim.x + threadIdx.x, l = blockIdx.y;
+    if (e >= H * H) return;
+    const int i = e / H, j = e - i * H;
+    const __bf16 w = (__bf16)p[off_weight(in, H, l + 1) + e];
+    const size_t HH = (size_t)H * H;
+    wf[l * HH + frag_pos(j, i, H >> 4)] = w;
+    wb[l * HH + frag_pos(i, j, H >> 4)] = w;
 }
 
 }  // namespace
@@ -321,6 +713,10 @@ struct mlp_handle {
     int Smax = 1;
     float* cpart = nullptr;            // column-sum partials [Zmax][kColK][H]
     int crow = 64;                     // rows per column-sum chunk
+    bool fused = false;                // the network runs as k_net / k_grad
+    __bf16 *wf = nullptr, *wb = nullptr, *actf = nullptr, *df = nullptr;
+    float *dg = nullptr, *part = nullptr, *xin = nullptr, *yin = nullptr;
+    int cap = 0;                       // rows that xin and yin hold
     float *dx = nullptr, *dt = nullptr;   // training rows of the last mlp_fit call
     int64_t data_cap = 0;
     int64_t steps = 0;
@@ -406,6 +802,54 @@ void backward(mlp_handle* h, const float* x, const float* t, int B, int nvalid)
     colsum(h, h->dpre, H, B, H, x, h->cfg.in_dim, h->cfg.in_dim, 1, h->g + h->off_W[0]);
 }
 
+// ---- fused pass
+int net_threads(const mlp_handle* h) { return 64 * std::min(8, h->H / 32); }
+size_t net_lds(const mlp_handle* h) { return (size_t)2 * kRows * (h->H + kPadH) * sizeof(__bf16); }
+
+NetArgs net_args(const mlp_handle* h, const float* x, const float* t, int nvalid)
+{
+    NetArgs a{};
+    a.p = h->p; a.wf = h->wf; a.wb = h->wb; a.X = x; a.T = t;
+    a.in = h->cfg.in_dim; a.H = h->H; a.nl = h->nl; a.nvalid = nvalid;
+    a.nb = (nvalid + kRows - 1) / kRows;
+    a.dg = h->dg; a.actf = h->actf; a.df = h->df; a.part = h->part;
+    return a;
+}
+
+// loss and gradient of the rows of `a`, into h->g and h->loss, or (adam) a step on them
+void train_pass(mlp_handle* h, const NetArgs& a, const AdamArgs* adam)
+{
+    const int H = h->H, nl = h->nl, in = a.in;
+    hipLaunchKernelGGL(k_net<true>, dim3(a.nb), dim3(net_threads(h)), net_lds(h), h->stream, a);
+    // spans of at least 256 rows, at most 16 of them, one per wave
+    const int K = (a.nb * kRows + 63) / 64 * 64;
+    int S = 1;
+    while (S < 16 && K % (64 * S) == 0 && K / (2 * S) >= 256) S *= 2;
+    const int threads = std::max(256, 64 * S);
+    const size_t lds = (size_t)S * 1024 * 4;
+    const dim3 grid((nl - 1) * (H / 32) * (H / 32) + (part_size(in, H, nl) + 15) / 16);
+    if (adam)
+        hipLaunchKernelGGL(k_grad<true>, grid, dim3(threads), lds, h->stream, h->p, h->g, h->wf, h->wb, a.actf, a.df, S,
+                           K / S / kRows, a.part, a.nb, in, H, nl, h->loss, *adam);
+    else
+        hipLaunchKernelGGL(k_grad<false>, grid, dim3(threads), lds, h->stream, h->p, h->g, h->wf, h->wb, a.actf, a.df, S,
+                           K / S / kRows, a.part, a.nb, in, H, nl, h->loss, AdamArgs{});
+}
+
+// the BF16 copies of the hidden matrices, after the FP32 parameters were written
+void refresh16(mlp_handle* h)
+{
+    const int HH = h->H * h->H;
+    if (h->fused) {
+        if (h->nl > 1)
+            hipLaunchKernelGGL(k_pack, dim3((HH + 255) / 256, h->nl - 1), dim3(256), 0, h->stream, h->p, h->cfg.in_dim, h->H,
+                               h->wf, h->wb);
+        return;
+    }
+    for (int l = 1; l < h->nl; ++l)
+        hipLaunchKernelGGL(k_to_bf16, grid1(HH), dim3(256), 0, h->stream, h->p + h->off_W[l], h->p16 + h->off16[l], HH);
+}
+
 }  // namespace
 
 extern "C" {
@@ -471,28 +915,46 @@ rewl_status mlp_create(const mlp_config* c, void* hip_stream, mlp_handle** out)
     if (s == REWL_OK) s = h->alloc(&h->g, h->P);
     if (s == REWL_OK) s = h->alloc(&h->m, h->P);
     if (s == REWL_OK) s = h->alloc(&h->v, h->P);
-    if (s == REWL_OK) s = h->alloc(&h->p16, h->n16);
-    if (s == REWL_OK) s = h->alloc(&h->map16, h->P);
-    h->pre.assign(h->nl, nullptr);
-    h->act.assign(h->nl, nullptr);
-    for (int l = 0; l < h->nl && s == REWL_OK; ++l) {
-        s = h->alloc(&h->pre[l], BH);
-        if (s == REWL_OK) s = h->alloc(&h->act[l], BH);
-    }
-    if (s == REWL_OK) s = h->alloc(&h->dpre, BH);
-    if (s == REWL_OK) s = h->alloc(&h->dtmp, BH);
-    if (s == REWL_OK) s = h->alloc(&h->d16a, BH);
-    if (s == REWL_OK) s = h->alloc(&h->d16b, BH);
-    if (s == REWL_OK) s = h->alloc(&h->y, h->Bmax);
-    if (s == REWL_OK) s = h->alloc(&h->dy, h->Bmax);
+    h->fused = H <= kFusedMaxH;
     if (s == REWL_OK) s = h->alloc(&h->loss, 1);
     if (s == REWL_OK) s = h->alloc(&h->xb, (size_t)h->Bmax * c->in_dim);
     if (s == REWL_OK) s = h->alloc(&h->yb, h->Bmax);
-    // split-K partials: at most 16 splits and 64 MiB
-    while (h->Smax < 16 && (size_t)2 * h->Smax * H * H * 4 <= ((size_t)64 << 20)) h->Smax *= 2;
-    if (s == REWL_OK && h->Smax > 1) s = h->alloc(&h->kpart, (size_t)h->Smax * H * H);
-    h->crow = std::max(16, h->Bmax / 1024);
-    if (s == REWL_OK) s = h->alloc(&h->cpart, (size_t)((h->Bmax + h->crow - 1) / h->crow) * kColK * H);
+    if (h->fused) {
+        const size_t nh = h->nl - 1;                   // hidden matrices
+        if (s == REWL_OK) s = h->alloc(&h->wf, nh * H * H);
+        if (s == REWL_OK) s = h->alloc(&h->wb, nh * H * H);
+        if (s == REWL_OK) s = h->alloc(&h->dg, h->nl * BH);
+        if (s == REWL_OK) s = h->alloc(&h->actf, nh * BH);
+        if (s == REWL_OK) s = h->alloc(&h->df, nh * BH);
+        if (s == REWL_OK) s = h->alloc(&h->part, (size_t)(h->Bmax / kRows) * part_size(c->in_dim, H, h->nl));
+        h->cap = std::max(h->Bmax, 1 << 16);           // inference: rows per upload
+        if (s == REWL_OK) s = h->alloc(&h->xin, (size_t)h->cap * c->in_dim);
+        if (s == REWL_OK) s = h->alloc(&h->yin, h->cap);
+        const int lds = 2 * kRows * (kFusedMaxH + kPadH) * (int)sizeof(__bf16);
+        if (hipFuncSetAttribute((const void*)k_net<true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess ||
+            hipFuncSetAttribute((const void*)k_net<false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+            return bail(mfail(REWL_E_DEVICE, "cannot raise the dynamic LDS limit"));
+    } else {
+        if (s == REWL_OK) s = h->alloc(&h->p16, h->n16);
+        if (s == REWL_OK) s = h->alloc(&h->map16, h->P);
+        h->pre.assign(h->nl, nullptr);
+        h->act.assign(h->nl, nullptr);
+        for (int l = 0; l < h->nl && s == REWL_OK; ++l) {
+            s = h->alloc(&h->pre[l], BH);
+            if (s == REWL_OK) s = h->alloc(&h->act[l], BH);
+        }
+        if (s == REWL_OK) s = h->alloc(&h->dpre, BH);
+        if (s == REWL_OK) s = h->alloc(&h->dtmp, BH);
+        if (s == REWL_OK) s = h->alloc(&h->d16a, BH);
+        if (s == REWL_OK) s = h->alloc(&h->d16b, BH);
+        if (s == REWL_OK) s = h->alloc(&h->y, h->Bmax);
+        if (s == REWL_OK) s = h->alloc(&h->dy, h->Bmax);
+        // split-K partials: at most 16 splits and 64 MiB
+        while (h->Smax < 16 && (size_t)2 * h->Smax * H * H * 4 <= ((size_t)64 << 20)) h->Smax *= 2;
+        if (s == REWL_OK && h->Smax > 1) s = h->alloc(&h->kpart, (size_t)h->Smax * H * H);
+        h->crow = std::max(16, h->Bmax / 1024);
+        if (s == REWL_OK) s = h->alloc(&h->cpart, (size_t)((h->Bmax + h->crow - 1) / h->crow) * kColK * H);
+    }
     if (s != REWL_OK) return bail(s);
     // initial weights: uniform(-1/sqrt(fan_in), 1/sqrt(fan_in)) from a fixed hash, biases 0
     std::vector<float> p0(h->P, 0.f);
@@ -514,12 +976,10 @@ rewl_status mlp_create(const mlp_config* c, void* hip_stream, mlp_handle** out)
         }
     for (int j = 0; j < H; ++j) p0[h->off_wout + j] = uni() / std::sqrt((float)H);
     if (hipMemcpy(h->p, p0.data(), h->P * 4, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(h->map16, map.data(), h->P * 4, hipMemcpyHostToDevice) != hipSuccess ||
+        (h->map16 && hipMemcpy(h->map16, map.data(), h->P * 4, hipMemcpyHostToDevice) != hipSuccess) ||
         hipMemset(h->m, 0, h->P * 4) != hipSuccess || hipMemset(h->v, 0, h->P * 4) != hipSuccess)
         return bail(mfail(REWL_E_DEVICE, "initial upload failed"));
-    for (int l = 1; l < h->nl; ++l)
-        hipLaunchKernelGGL(k_to_bf16, grid1(H * H), dim3(256), 0, h->stream, h->p + h->off_W[l],
-                           h->p16 + h->off16[l], H * H);
+    refresh16(h);
     if (hipStreamSynchronize(h->stream) != hipSuccess) return bail(mfail(REWL_E_DEVICE, "init failed"));
     *out = h;
     return REWL_OK;
@@ -544,9 +1004,7 @@ rewl_status mlp_set_params(mlp_handle* h, const float* host, size_t n)
 {
     if (!h || !host || n != (size_t)h->P) return mfail(REWL_E_INVALID, "need n = parameter count");
     MLP_TRY(hipMemcpyAsync(h->p, host, n * 4, hipMemcpyHostToDevice, h->stream));
-    for (int l = 1; l < h->nl; ++l)
-        hipLaunchKernelGGL(k_to_bf16, grid1(h->H * h->H), dim3(256), 0, h->stream, h->p + h->off_W[l],
-                           h->p16 + h->off16[l], h->H * h->H);
+    refresh16(h);
     MLP_TRY(hipStreamSynchronize(h->stream));
     return REWL_OK;
 }
@@ -556,6 +1014,19 @@ rewl_status mlp_infer(mlp_handle* h, const float* x, float* y, int32_t B)
 {
     if (!h || (B > 0 && (!x || !y)) || B < 0) return mfail(REWL_E_INVALID, "bad arguments");
     const int in = h->cfg.in_dim;
+    if (h->fused) {
+        for (int64_t r0 = 0; r0 < B; r0 += h->cap) {
+            const int nb = (int)std::min<int64_t>(h->cap, B - r0);
+            MLP_TRY(hipMemcpyAsync(h->xin, x + (size_t)r0 * in, (size_t)nb * in * 4, hipMemcpyHostToDevice, h->stream));
+            NetArgs a = net_args(h, h->xin, nullptr, nb);
+            a.y = h->yin;
+            hipLaunchKernelGGL(k_net<false>, dim3(a.nb), dim3(net_threads(h)), net_lds(h), h->stream, a);
+            MLP_TRY(hipGetLastError());
+            MLP_TRY(hipMemcpyAsync(y + r0, h->yin, (size_t)nb * 4, hipMemcpyDeviceToHost, h->stream));
+            MLP_TRY(hipStreamSynchronize(h->stream));
+        }
+        return REWL_OK;
+    }
     for (int r0 = 0; r0 < B; r0 += h->Bmax) {
         const int nb = std::min(h->Bmax, B - r0);
         const int Bp = (nb + 63) / 64 * 64;
@@ -574,12 +1045,18 @@ rewl_status mlp_grad(mlp_handle* h, const float* x, const float* t, int32_t B, f
 {
     if (!h || !x || !t || B < 1 || B > h->Bmax) return mfail(REWL_E_INVALID, "need 1 <= B <= max_batch");
     const int in = h->cfg.in_dim, Bp = (B + 63) / 64 * 64;
-    MLP_TRY(hipMemsetAsync(h->xb, 0, (size_t)Bp * in * 4, h->stream));
-    MLP_TRY(hipMemsetAsync(h->yb, 0, (size_t)Bp * 4, h->stream));
+    if (!h->fused) {
+        MLP_TRY(hipMemsetAsync(h->xb, 0, (size_t)Bp * in * 4, h->stream));
+        MLP_TRY(hipMemsetAsync(h->yb, 0, (size_t)Bp * 4, h->stream));
+    }
     MLP_TRY(hipMemcpyAsync(h->xb, x, (size_t)B * in * 4, hipMemcpyHostToDevice, h->stream));
     MLP_TRY(hipMemcpyAsync(h->yb, t, (size_t)B * 4, hipMemcpyHostToDevice, h->stream));
-    forward(h, h->xb, Bp);
-    backward(h, h->xb, h->yb, Bp, B);
+    if (h->fused) {
+        train_pass(h, net_args(h, h->xb, h->yb, B), nullptr);
+    } else {
+        forward(h, h->xb, Bp);
+        backward(h, h->xb, h->yb, Bp, B);
+    }
     MLP_TRY(hipGetLastError());
     if (grad_host) MLP_TRY(hipMemcpyAsync(grad_host, h->g, h->P * 4, hipMemcpyDeviceToHost, h->stream));
     if (loss) MLP_TRY(hipMemcpyAsync(loss, h->loss, 4, hipMemcpyDeviceToHost, h->stream));
@@ -608,12 +1085,21 @@ rewl_status mlp_fit(mlp_handle* h, const float* x, const float* t, int64_t n, in
     MLP_TRY(hipMemcpyAsync(h->dt, t, (size_t)n * 4, hipMemcpyHostToDevice, h->stream));
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
     for (int64_t s = 0; s < steps; ++s) {
+        const int64_t now = h->steps++;
+        const float c1 = 1.f - std::pow(b1, (float)h->steps), c2 = 1.f - std::pow(b2, (float)h->steps);
+        if (h->fused) {
+            NetArgs a = net_args(h, h->dx, h->dt, B);
+            a.gather = (int)n;
+            a.seed = seed;
+            a.step = (uint64_t)now;
+            const AdamArgs ad{h->m, h->v, lr, b1, b2, eps, c1, c2};
+            train_pass(h, a, &ad);
+            continue;
+        }
         hipLaunchKernelGGL(k_gather, grid1(B), dim3(256), 0, h->stream, h->dx, h->dt, in, (int)n, B,
-                           (uint64_t)h->steps, seed, h->xb, h->yb);
+                           (uint64_t)now, seed, h->xb, h->yb);
         forward(h, h->xb, B);
         backward(h, h->xb, h->yb, B, B);
-        h->steps += 1;
-        const float c1 = 1.f - std::pow(b1, (float)h->steps), c2 = 1.f - std::pow(b2, (float)h->steps);
         hipLaunchKernelGGL(k_adam, grid1(h->P), dim3(256), 0, h->stream, h->p, h->g, h->m, h->v, h->P,
                            lr, b1, b2, eps, c1, c2, h->p16, h->map16);
     }

@@ -262,3 +262,53 @@ def test_warm_table_matches_oracle(net, model, q, L):
     x = M.encode_bins(model, q, L).astype(np.float32).astype(np.float64)
     yo, sy = forward_sigma(device_weights(p, *SHAPE), x, *SHAPE)
     assert (np.abs(tab - N * yo) <= N * (K_SIGMA * sy + 2 ** -20 * np.max(np.abs(yo))) + 2 ** -17).all()
+
+
+# Shapes at the edges of the fused pass (16 rows per block, up to 8 waves of 32-column
+# tiles, 64- and 128-wide K chunks, spans of 256 rows and more for the weight gradients)
+# and, from hidden = 1088 on, of the layer-by-layer kernels.  Same bounds as above.
+@pytest.mark.parametrize("shape,B", [((1, 64, 1), 5), ((3, 64, 2), 16), ((3, 192, 2), 17), ((16, 320, 2), 48),
+                                     ((2, 128, 4), 15), ((3, 1024, 2), 33), ((3, 1088, 2), 20),
+                                     ((3, 64, 2), 511), ((3, 64, 2), 1030), ((3, 64, 2), 4100)])
+def test_shapes_match_oracle(rw, shape, B):
+    net = rw.Mlp(*shape, max_batch=B, seed=4)
+    try:
+        p = params(*shape, seed=61)
+        net.set_params(p)
+        x, t = rows(B, shape[0], seed=62)
+        pw = device_weights(p, *shape)
+        yo, sy = forward_sigma(pw, x, *shape)
+        assert within(net.infer(x).astype(np.float64), yo, sy).all()
+        g, loss = net.grad(x, t)
+        go, sg = grad_sigma(pw, x, t, *shape, samples=64)
+        assert within(g.astype(np.float64), go, sg, k=8.0).all()
+        assert loss == pytest.approx(M.grad(pw, x, t, *shape)[1], rel=1e-2)
+        assert np.array_equal(g, net.grad(x, t)[0])                      # every sum has a fixed order
+    finally:
+        net.close()
+
+
+@pytest.mark.parametrize("shape", [(5, 320, 3), (3, 64, 1), (3, 1088, 2)])
+def test_adam_steps_of_shapes(rw, shape):
+    # as test_adam_steps_match_oracle; the step must also refresh the BF16 weights: the
+    # outputs after it are those of a network given the stepped parameters
+    net, other = rw.Mlp(*shape, max_batch=128, seed=2), rw.Mlp(*shape, max_batch=128, seed=9)
+    try:
+        p = params(*shape, seed=71)
+        net.set_params(p)
+        x, t = rows(1, shape[0], seed=72)
+        X, T = np.repeat(x, 128, axis=0), np.repeat(t, 128)
+        lr, m, v, po = 1e-3, np.zeros_like(p), np.zeros_like(p), p.copy()
+        for step in (1, 2):
+            g, _ = net.grad(X, T)
+            net.fit(X, T, steps=1, batch=128, lr=lr, seed=7)
+            po_new, m, v = M.adam_step(po, g.astype(np.float64), m, v, step, lr)
+            pd = net.params().astype(np.float64)
+            assert np.all(np.abs(pd - po_new) <= 1e-4 * lr + 2 ** -23 * np.abs(po_new))
+            po = pd
+        other.set_params(net.params())
+        xi, _ = rows(50, shape[0], seed=73)
+        assert np.array_equal(net.infer(xi), other.infer(xi))
+    finally:
+        net.close()
+        other.close()
