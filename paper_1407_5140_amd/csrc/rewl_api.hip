@@ -165,8 +165,6 @@ struct rewl_handle {
     size_t max_lds_wave = 0;
     int2* d_merge = nullptr;
     int nmerge = 0;
-    int32_t* d_rng_start = nullptr;
-    int rng_grid = 0;
     int32_t* d_exch_start = nullptr;
     int exch_threads = 0;
     int32_t* d_slot_start = nullptr;
@@ -248,15 +246,12 @@ bool plan_wave(int model, int L, int N, int WB, int m, int64_t S, const rewl_tun
 rewl_status enqueue_interval(rewl_handle* H, bool time_it)
 {
     if (time_it) HIP_TRY(hipEventRecord(H->ev[0], H->stream));
-    if (H->rng_grid > 0)
-        hipLaunchKernelGGL(k_rng, dim3(H->rng_grid), dim3(256), 0, H->stream, H->d_insts,
-                           H->d_rng_start, H->n);
     if (time_it) HIP_TRY(hipEventRecord(H->ev[1], H->stream));
     if (H->ntiles > 0 && H->tune.persistent)
-        hipLaunchKernelGGL(k_sweep_persist, dim3(H->persist_grid), dim3(64), H->max_lds, H->stream, H->d_insts,
+        hipLaunchKernelGGL(k_sweep_persist, dim3(H->persist_grid), dim3(128), H->max_lds, H->stream, H->d_insts,
                            H->d_tiles, H->ntiles, H->d_queue);
     else if (H->ntiles > 0)
-        hipLaunchKernelGGL(k_sweep, dim3(H->ntiles), dim3(64), H->max_lds, H->stream, H->d_insts,
+        hipLaunchKernelGGL(k_sweep, dim3(H->ntiles), dim3(128), H->max_lds, H->stream, H->d_insts,
                            H->d_tiles, H->ntiles);
     if (H->nwtiles > 0)
         hipLaunchKernelGGL(k_sweep_wave, dim3(H->nwtiles), dim3(H->wave_threads), H->max_lds_wave,
@@ -565,7 +560,7 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
     std::vector<Inst> devs(n);
     std::vector<Tile> tiles, wtiles;
     std::vector<int2> merges;
-    std::vector<int32_t> rng_start(1, 0), exch_start(1, 0), slot_start(1, 0);
+    std::vector<int32_t> exch_start(1, 0), slot_start(1, 0);
     auto bail = [&](rewl_status s) {
         rewl_destroy(H);
         return s;
@@ -651,8 +646,7 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
         d.band = band;
         d.hglobal = hi.placement == REWL_TABLE_DEVICE ? 1 : 0;
         d.mapn = hi.kind == REWL_SWEEP_WAVE ? hi.mapn : 0;
-        d.XP = (c.exchange_interval + 31) / 32 * 32;   // two draw chunks of 16
-        if ((uint64_t)d.XP * hi.S >= (uint64_t(1) << 32))
+        if ((uint64_t)((c.exchange_interval + 31) / 32 * 32) * hi.S >= (uint64_t(1) << 32))
             return bail(fail(REWL_E_INVALID, "instance " + std::to_string(i) + ": walkers x interval exceeds 2^32 draws"));
         const size_t S = hi.S, h = hi.h, WB = hi.WB;
         rewl_status s = REWL_OK;
@@ -669,9 +663,6 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
         if (s == REWL_OK) s = H->alloc(&d.done, h);
         if (s == REWL_OK) s = H->alloc(&d.flat, S);
         if (s == REWL_OK) s = H->alloc(&d.swaps, S);
-        const size_t ndraw = hi.kind == REWL_SWEEP_LANE ? (size_t)d.XP * S : 1;
-        if (s == REWL_OK) s = H->alloc(&d.rpack, ndraw);
-        if (s == REWL_OK) s = H->alloc(&d.rv, ndraw);
         if (s == REWL_OK) s = H->alloc(&d.ex_prop, h);
         if (s == REWL_OK) s = H->alloc(&d.ex_acc, h);
         if (s == REWL_OK) s = H->alloc(&d.merges, h);
@@ -713,11 +704,6 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
             for (int r0 = 0; r0 < hi.m; r0 += hi.wpb)
                 (hi.kind == REWL_SWEEP_LANE ? tiles : wtiles).push_back({i, a, r0, hi.wpb});
         }
-        const int64_t work = c.exchange_interval * (int64_t)S;
-        const int64_t nb = hi.kind != REWL_SWEEP_LANE
-                               ? 0
-                               : std::min<int64_t>(std::max<int64_t>((work + 2047) / 2048, 1), 16384);
-        rng_start.push_back(rng_start.back() + (int32_t)nb);
         exch_start.push_back(exch_start.back() + ((c.exchange_enabled && hi.h > 1) ? (hi.h - 1) * hi.m : 0));
         slot_start.push_back(slot_start.back() + hi.S);
     }
@@ -744,14 +730,12 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
     H->ntiles = (int)tiles.size();
     H->nwtiles = (int)wtiles.size();
     H->nmerge = (int)merges.size();
-    H->rng_grid = rng_start.back();
     H->exch_threads = exch_start.back();
     H->slot_threads = slot_start.back();
     if ((s = H->alloc(&H->d_insts, n)) != REWL_OK) return bail(s);
     if ((s = H->alloc(&H->d_tiles, tiles.size())) != REWL_OK) return bail(s);
     if ((s = H->alloc(&H->d_wtiles, wtiles.size())) != REWL_OK) return bail(s);
     if ((s = H->alloc(&H->d_merge, merges.size())) != REWL_OK) return bail(s);
-    if ((s = H->alloc(&H->d_rng_start, rng_start.size())) != REWL_OK) return bail(s);
     if ((s = H->alloc(&H->d_exch_start, exch_start.size())) != REWL_OK) return bail(s);
     if ((s = H->alloc(&H->d_slot_start, slot_start.size())) != REWL_OK) return bail(s);
     bool ok = true;
@@ -762,7 +746,6 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
     if (!wtiles.empty())
         ok &= hipMemcpyAsync(H->d_wtiles, wtiles.data(), sizeof(Tile) * wtiles.size(), hipMemcpyHostToDevice, st) == hipSuccess;
     ok &= hipMemcpyAsync(H->d_merge, merges.data(), sizeof(int2) * merges.size(), hipMemcpyHostToDevice, st) == hipSuccess;
-    ok &= hipMemcpyAsync(H->d_rng_start, rng_start.data(), 4 * rng_start.size(), hipMemcpyHostToDevice, st) == hipSuccess;
     ok &= hipMemcpyAsync(H->d_exch_start, exch_start.data(), 4 * exch_start.size(), hipMemcpyHostToDevice, st) == hipSuccess;
     ok &= hipMemcpyAsync(H->d_slot_start, slot_start.data(), 4 * slot_start.size(), hipMemcpyHostToDevice, st) == hipSuccess;
     ok &= hipStreamSynchronize(st) == hipSuccess;
@@ -777,7 +760,7 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
 
     if (H->ntiles > 0) {
         int per_cu = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)k_sweep_persist, 64,
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)k_sweep_persist, 128,
                                                          std::max<size_t>(H->max_lds, 1)) != hipSuccess)
             return bail(fail(REWL_E_DEVICE, "occupancy query failed"));
         H->persist_grid = std::max(1, std::min(H->ntiles, std::max(per_cu, 1) * n_cu));

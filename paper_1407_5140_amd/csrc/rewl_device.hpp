@@ -177,6 +177,23 @@ __device__ __forceinline__ Bound32 bounds_of(uint32_t z, uint32_t w, float band)
     return {w ? lo : -0x1.fffffep+127f, w ? hi : __builtin_inff()};
 }
 
+// The same as one word per draw, for a delta rounded to FP32: delta > hi accepts,
+// delta < lower_of(hi, e) rejects, e = kErrLane + band.  The rounding of delta (2^-19 up
+// to 64) is inside e, the logarithm's error inside the factors; at w = 0 the FP64
+// logarithm is taken, and u53 = 0 (every finite delta accepts) gives the lowest float.
+constexpr float kErrLane = 0x1p-17f;
+__device__ __forceinline__ float upper_of(uint32_t z, uint32_t w, float e)
+{
+    const float u = __builtin_fmaf((float)z, 0x1p-32f, (float)w) * 0x1p-32f;
+    float l = __builtin_amdgcn_logf(u) * 0.693147181f;
+    if (__builtin_expect(w == 0, 0)) {
+        if (z >> 11 == 0) return -0x1.fffffep+127f;
+        l = (float)log(__builtin_ldexp((double)(z >> 11), -53));
+    }
+    return __builtin_fmaf(l, 1.0f - 0x1p-20f, e);
+}
+__device__ __forceinline__ float lower_of(float hi, float e) { return __builtin_fmaf(hi, 1.0f + 0x1p-18f, -3.0f * e); }
+
 // ---------------------------------------------------------- descriptors
 enum : int32_t { kErrOverflow = 1, kErrInitStuck = 2, kErrExactness = 4 };
 
@@ -197,7 +214,6 @@ struct Inst {
     int32_t model, q, L, N, W, h, m, S, WB, log2m;
     int32_t flat_num, flat_den, kfinal, exch, wpr, flat_rule;
     int64_t X;
-    int64_t XP;         // row stride of the draw buffers: X rounded up to 32
     uint32_t k0, k1;
     // device arrays
     uint64_t* lat;      // Ising: [S][L*wpr] words, bit x of row y's word = spin up
@@ -214,9 +230,6 @@ struct Inst {
     int32_t* done;      // [h]
     uint8_t* flat;      // [S]   latched flatness
     int8_t* swaps;      // [S]   last interval: 1 swapped, 0 rejected, -1 none
-    uint32_t* rpack;    // [S][XP] Ising: row | col<<8 | row_up<<16 | row_down<<24;
-                        //         Potts: row | col<<8 | proposal offset<<16
-    double* rv;         // [S][XP] threshold log(u53 2^-53) + band
     int64_t* ex_prop;   // [h]
     int64_t* ex_acc;    // [h]
     int32_t* merges;    // [h] interval of each window's last merge

@@ -1,10 +1,9 @@
 // rewl_kernels.hip -- the REWL hot path on gfx950.
 //
 // One interval of replica-exchange Wang-Landau (arXiv:1407.5140 Sec. II.A):
-//   k_rng      Philox draws of every flip attempt of the interval (whole GPU)
 //   k_sweep    X single-site attempts per walker, one walker per lane, the
 //              walker's lattice and histogram and its window's ln g base in LDS,
-//              flatness test of every walker in the epilogue
+//              drawn by a second wave; flatness test of every walker in the epilogue
 //   k_merge    per window: when all m walkers are flat, average ln g, reset H,
 //              halve ln f, detect convergence
 //   k_exchange Eq. (1) between neighbouring windows, alternating pairings
@@ -15,85 +14,34 @@
 
 namespace rewl {
 
-// --------------------------------------------------------------------- RNG
-// For instance i, walker row `slot` holds the interval's X draws contiguously
-// (row stride XP = X rounded up to the sweep's chunk pair): entry slot*XP + j
-// has site = floor(x0 N / 2^32), row = site / L, col = site % L, and
-//   Ising pack = row | col<<8 | row_up<<16 | row_down<<24 (periodic rows),
-//   Potts pack = row | col<<8 | off<<16, off = floor(x1 (q-1) / 2^32),
-// and the acceptance threshold of u53 (threshold_of).  Consecutive threads take
-// consecutive j (coalesced stores).
-__global__ void __launch_bounds__(256) k_rng(const Inst* __restrict__ insts,
-                                             const int32_t* __restrict__ block_start, int n_inst)
-{
-    int lo = 0, hi = n_inst - 1;
-    const int b = blockIdx.x;
-    while (lo < hi) {                          // instance owning this block
-        int mid = (lo + hi + 1) >> 1;
-        if (block_start[mid] <= b) lo = mid;
-        else hi = mid - 1;
-    }
-    const Inst& I = insts[lo];
-    if (I.ctr->all_done) return;
-    const uint32_t X = (uint32_t)I.X, XP = (uint32_t)I.XP;
-    const uint32_t n = X * (uint32_t)I.S;      // < 2^32, checked at creation
-    const uint32_t nthreads = (uint32_t)(block_start[lo + 1] - block_start[lo]) * blockDim.x;
-    const uint64_t T0 = (uint64_t)I.ctr->t * (uint64_t)X;
-    const uint32_t N = I.N, L = I.L, qm1 = I.q - 1;
-    const float rL = 1.0f / (float)L;
-    // element e = slot X + j, walked with stride nthreads = sq X + sr: the
-    // division happens once per thread, then slot and j advance by adds
-    const uint32_t e0 = (uint32_t)(b - block_start[lo]) * blockDim.x + threadIdx.x;
-    const uint32_t sq = nthreads / X, sr = nthreads - sq * X;
-    uint32_t slot = e0 / X, j = e0 - slot * X;
-    for (uint64_t e = e0; e < n; e += nthreads) {
-        const u32x4 x = draw(I.k0, I.k1, T0 + j, slot, kTagFlip);
-        const uint32_t site = (uint32_t)(((uint64_t)x.x * N) >> 32);
-        // row = site / L: site < 2^24 is exact in FP32, the product's rounding
-        // puts the estimate at most one off, corrected below
-        uint32_t row = (uint32_t)((float)site * rL);
-        int32_t col = (int32_t)site - (int32_t)(row * L);
-        if (col < 0) { --row; col += (int32_t)L; }
-        else if (col >= (int32_t)L) { ++row; col -= (int32_t)L; }
-        uint32_t pack;
-        if (I.model) {
-            pack = row | ((uint32_t)col << 8) | ((uint32_t)(((uint64_t)x.y * qm1) >> 32) << 16);
-        } else {
-            const uint32_t ru = row == 0 ? L - 1 : row - 1, rd = row == L - 1 ? 0 : row + 1;
-            pack = row | ((uint32_t)col << 8) | (ru << 16) | (rd << 24);
-        }
-        const size_t idx = (size_t)slot * XP + j;
-        I.rpack[idx] = pack;
-        I.rv[idx] = threshold_of(u53_of(x), I.band);
-        slot += sq;
-        j += sr;
-        if (j >= X) { j -= X; ++slot; }
-    }
-}
-
 // ------------------------------------------------------------------- sweep
 // LDS of one tile of nw walkers of window a:
 //   base [kPad + WB + kPad]         window ln g base, +inf in the pads
 //   H    [(kPad + WB + kPad) << lnw] per-walker counts, bin-major (lane minor)
 //   lat  Ising [L*wpr << lnw] u64 words / Potts [N << lnw] bytes
+//   draws [2][8 (Ising) or 4 (Potts) << lnw]: the next attempts of every walker, twice
+// A block is two waves: wave 0 walks, wave 1 draws the next attempts of its walkers
+// meanwhile, down to the sites whose spins an attempt reads.  (Drawn by the whole GPU in a launch of its own, through a buffer
+// of 12 bytes per attempt in memory, the 65 280-walker batch took 3.9 + 13.1 ms per
+// interval, now 11.3.)
 // A move changes the bin by at most 2 (Ising) or 4 (Potts), so a proposal
 // outside the window lands in a pad, sees ln g = +inf and is rejected.
 constexpr int kPad = 4;
+constexpr int kDrawBytes = 64;      // of one walker: 8 draws of 8 bytes or 4 of 16
 
 __host__ __device__ inline size_t sweep_lds_bytes(int model, int L, int wpr, int WB, int nw)
 {
     const size_t nb = (size_t)WB + 2 * kPad;
-    size_t s = nb * 8 + nb * nw * 4;
-    s = (s + 7) & ~size_t(7);
-    s += model == 0 ? (size_t)L * wpr * nw * 8 : (size_t)L * L * nw;
-    return s;
+    size_t s = (nb * 8 + nb * nw * 4 + 15) & ~size_t(15);
+    s += ((model == 0 ? (size_t)L * wpr * 8 : (size_t)L * L) * nw + 15) & ~size_t(15);
+    return s + (size_t)2 * kDrawBytes * nw;
 }
 
-// Exact acceptance for the lanes whose fast test fell inside the guard band:
-// re-draw the attempt's u53 from its Philox counter and decide exactly.
-__device__ __noinline__ bool slow_decide(const Inst& I, uint64_t T, uint32_t slot, double delta)
+// How many bytes of the word x differ from the byte v.
+__device__ __forceinline__ int bytes_unlike(uint32_t x, uint32_t v)
 {
-    return accept_slow(delta, u53_of(draw(I.k0, I.k1, T, slot, kTagFlip)));
+    const uint32_t y = x ^ __builtin_amdgcn_perm(v, v, 0u);
+    return __builtin_popcount((((y & 0x7f7f7f7fu) + 0x7f7f7f7fu) | y) & 0x80808080u);
 }
 
 // The decision of decide_fast and accept_slow on the attempt's own draw: bit 0
@@ -104,16 +52,6 @@ __device__ __noinline__ int decide_draw(const Inst& I, uint64_t T, uint32_t slot
     const uint64_t u53 = u53_of(draw(I.k0, I.k1, T, slot, kTagFlip));
     const int f = decide_fast(delta, threshold_of(u53, I.band), I.band);
     return f == 2 ? 2 | (accept_slow(delta, u53) ? 1 : 0) : f;
-}
-
-// Native vectors for the draw chunks, loaded from the global address space
-// (plain vector loads rather than flat addressing).
-typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-typedef double v2d __attribute__((ext_vector_type(2)));
-template <class T>
-__device__ __forceinline__ T gload(const T* p)
-{
-    return *(const __attribute__((address_space(1))) T*)p;
 }
 
 // Lane l's value of a wave-uniform lane index l (v_readlane).
@@ -137,14 +75,21 @@ __device__ __forceinline__ double rld(double v, int l)
 template <int MODEL, int WPR>
 __device__ void sweep_tile(const Inst& I, const Tile& tile, char* smem)
 {
-    const int a = tile.window, nw = tile.nw, lane = threadIdx.x;
+    const int a = tile.window, nw = tile.nw, tid = threadIdx.x, lane = tid & 63;
+    const bool walks = tid < 64;                                 // wave 0; wave 1 draws
     const int WB = I.WB, L = I.L, N = I.N;
     const int slot0 = a * I.m + tile.r0;
     const int lo = I.lo[a];
     const int nbins = WB + 2 * kPad;
     double* lbase = (double*)smem;                               // index kPad + bin
     uint32_t* lH = (uint32_t*)(lbase + nbins);                   // index (kPad + bin) << lnw | lane
-    char* latp = smem + ((nbins * 8 + (size_t)nbins * nw * 4 + 7) & ~size_t(7));
+    char* latp = smem + ((nbins * 8 + (size_t)nbins * nw * 4 + 15) & ~size_t(15));
+    // Ising: .x row | col<<8 | row_up<<16 | row_down<<24 (periodic rows);
+    // Potts: .x site | off<<16, off = floor(x1 (q-1) / 2^32), .y and .z the neighbours' sites;
+    // last word: the bound of the threshold (upper_of)
+    typedef uint32_t Draw __attribute__((ext_vector_type(MODEL ? 4 : 2)));
+    constexpr int kDraws = kDrawBytes / (int)sizeof(Draw);
+    Draw* ring = (Draw*)(latp + (((MODEL == 0 ? (size_t)L * WPR * 8 : (size_t)N) * nw + 15) & ~size_t(15)));
     const int nthr = blockDim.x;
     const int lnw = __builtin_ctz(nw);                           // nw is a power of two
 
@@ -160,7 +105,7 @@ __device__ void sweep_tile(const Inst& I, const Tile& tile, char* smem)
     // bins b >= width (a window narrower than WB) are outside the window: +inf
     // table (moves there are rejected) and the never-visited sentinel
     const int width = I.hi[a] - lo + 1;
-    for (int i = lane; i < nbins; i += nthr) {
+    for (int i = tid; i < nbins; i += nthr) {
         const int b = i - kPad;
         lbase[i] = (b >= 0 && b < width) ? I.base[(size_t)a * WB + b] : __builtin_inf();
     }
@@ -176,7 +121,7 @@ __device__ void sweep_tile(const Inst& I, const Tile& tile, char* smem)
     bool bad = false;
     for (int l = 0; l < nw; ++l) {
         const uint64_t cl = rl64(cw, l);
-        for (int i = lane; i < nbins; i += nthr) {
+        for (int i = tid; i < nbins; i += nthr) {
             const int b = i - kPad;
             uint32_t hv = 0;
             if (b >= 0 && b < WB) {
@@ -196,36 +141,74 @@ __device__ void sweep_tile(const Inst& I, const Tile& tile, char* smem)
         uint64_t* lat = (uint64_t*)latp;
         const int nwords = L * WPR;
         for (int l = 0; l < nw; ++l)
-            for (int w = lane; w < nwords; w += nthr) lat[(w << lnw) + l] = I.lat[(size_t)(slot0 + l) * nwords + w];
+            for (int w = tid; w < nwords; w += nthr) lat[(w << lnw) + l] = I.lat[(size_t)(slot0 + l) * nwords + w];
     } else {
         uint8_t* lat = (uint8_t*)latp;
         for (int l = 0; l < nw; ++l)
-            for (int w = lane; w < N; w += nthr) lat[(w << lnw) + l] = I.plat[(size_t)(slot0 + l) * N + w];
+            for (int w = tid; w < N; w += nthr) lat[(w << lnw) + l] = I.plat[(size_t)(slot0 + l) * N + w];
     }
-    __syncthreads();
-
     const int k = I.k[a];
     const uint32_t inc = I.done[a] == 0 ? 1u : 0u;               // converged: frozen
     const double scale = __builtin_ldexp(1.0, -k);
-    const int64_t X = I.X;
+    const uint32_t X = (uint32_t)I.X, nchunk = (X + kDraws - 1) / kDraws;
     const uint64_t T0 = (uint64_t)I.ctr->t * (uint64_t)X;
+    const float e32 = kErrLane + (float)I.band;
 
-    if (lane < nw) {
+    if (!walks) {
+        // entry i << lnw | l of a chunk: attempt i of the chunk, walker l, at the site
+        // floor(x0 N / 2^32)
+        const uint32_t qm1 = I.q - 1;
+        const float rL = 1.0f / (float)L;
+        for (uint32_t c = 0; c <= nchunk; ++c) {
+            if (c < nchunk) {
+                Draw* r = ring + (size_t)(c & 1) * kDraws * nw;
+                for (int e = lane; e < kDraws << lnw; e += 64) {
+                    const u32x4 x = draw(I.k0, I.k1, T0 + (uint64_t)(c * kDraws + (e >> lnw)),
+                                         (uint32_t)(slot0 + (e & (nw - 1))), kTagFlip);
+                    const uint32_t site = (uint32_t)(((uint64_t)x.x * (uint32_t)N) >> 32);
+                    // row = site / L: site < 2^24 is exact in FP32, the product's rounding
+                    // puts the estimate at most one off, corrected below
+                    int row = (int)((float)site * rL);
+                    int col = (int)site - (int)__umul24((uint32_t)row, (uint32_t)L);
+                    if (col < 0) { --row; col += L; }
+                    else if (col >= L) { ++row; col -= L; }
+                    const uint32_t hi = __builtin_bit_cast(uint32_t, upper_of(x.z, x.w, e32));
+                    if constexpr (MODEL) {
+                        const uint32_t off = (uint32_t)(((uint64_t)x.y * qm1) >> 32);
+                        const uint32_t up = row == 0 ? site + (N - L) : site - L;
+                        const uint32_t dn = row == L - 1 ? site - (N - L) : site + L;
+                        const uint32_t lf = col == 0 ? site + (L - 1) : site - 1;
+                        const uint32_t rt = col == L - 1 ? site - (L - 1) : site + 1;
+                        r[e] = Draw{site | (off << 16), up | (dn << 16), lf | (rt << 16), hi};
+                    } else {
+                        const int ru = row == 0 ? L - 1 : row - 1, rd = row == L - 1 ? 0 : row + 1;
+                        r[e] = Draw{(uint32_t)(row | (col << 8) | (ru << 16) | (rd << 24)), hi};
+                    }
+                }
+            }
+            __syncthreads();                  // chunk c is there, chunk c - 1 has been walked
+        }
+    } else {
+        __syncthreads();                      // everything is staged, and chunk 0 is there
         const int slot = slot0 + lane;
-        int b = I.bin[slot] - lo + kPad;                         // padded bin index
-        uint32_t hc = lH[(b << lnw) + lane];
+        const bool active = lane < nw;
+        int b = active ? I.bin[slot] - lo + kPad : kPad;         // padded bin index
+        const int wl = active ? lane : 0;
+        uint32_t hc = lH[(b << lnw) + wl];
         double lngc = __builtin_fma((double)hc, scale, lbase[b]);
         const double incv = inc ? scale : 0.0;
-        const double band2 = 2.0 * I.band;
 
-        // one flip attempt with the precomputed draw (pk, vb) of attempt j;
+        const int q = I.q;
+        // one flip attempt with draw D, attempt j;
         // lH always holds the walker's current counts, including bin b
-        auto attempt = [&](uint32_t pk, double vb, int64_t j) {
+        auto attempt = [&](const Draw& D, uint32_t j) {
+            const uint32_t pk = D.x, hw = D[MODEL ? 3 : 1];
+            const float hi = __builtin_bit_cast(float, hw);
             int nb;
             int waddr;                                           // LDS index of the flipped word/byte
-            uint64_t wnew = 0;
-            uint8_t pnew = 0;
-            if (MODEL == 0) {
+            uint64_t wold = 0, wnew = 0;
+            uint8_t pold = 0, pnew = 0;
+            if constexpr (MODEL == 0) {
                 const uint64_t* lat = (const uint64_t*)latp;
                 const int r = pk & 0xff, c = (pk >> 8) & 0xff;
                 const int ru = (pk >> 16) & 0xff, rd = pk >> 24;
@@ -240,6 +223,7 @@ __device__ void sweep_tile(const Inst& I, const Tile& tile, char* smem)
                                           ((uint32_t)(w >> cl) & 1u) + ((uint32_t)(w >> cr) & 1u);
                     // aligned neighbours al: dE = 4 al - 8, bin change al - 2
                     nb = b + (sp ? (int)ones : 4 - (int)ones) - 2;
+                    wold = w;
                     wnew = w ^ (1ull << c);
                 } else {
                     const int cl = c == 0 ? L - 1 : c - 1, cr = c == L - 1 ? 0 : c + 1;
@@ -251,98 +235,74 @@ __device__ void sweep_tile(const Inst& I, const Tile& tile, char* smem)
                     const uint32_t sp = (uint32_t)(w >> (c & 63)) & 1u;
                     const uint32_t ones = spin(ru, c) + spin(rd, c) + spin(r, cl) + spin(r, cr);
                     nb = b + (sp ? (int)ones : 4 - (int)ones) - 2;
+                    wold = w;
                     wnew = w ^ (1ull << (c & 63));
                 }
             } else {
-                const uint8_t* lat = (const uint8_t*)latp;
-                const int r = pk & 0xff, c = (pk >> 8) & 0xff;
-                const int site = (int)__umul24((uint32_t)r, (uint32_t)L) + c;
-                const int up = r == 0 ? site + N - L : site - L;
-                const int dn = r == L - 1 ? site - N + L : site + L;
-                const int lf = c == 0 ? site + L - 1 : site - 1;
-                const int rt = c == L - 1 ? site - L + 1 : site + 1;
-                waddr = (site << lnw) + lane;
-                const int s0 = lat[waddr];
-                const int n0 = lat[(up << lnw) + lane];
-                const int n1 = lat[(dn << lnw) + lane];
-                const int n2 = lat[(lf << lnw) + lane];
-                const int n3 = lat[(rt << lnw) + lane];
-                int nv = s0 + 1 + (int)(pk >> 16);
-                nv = nv >= I.q ? nv - I.q : nv;
+                const uint8_t* lat = (const uint8_t*)latp + lane;
+                waddr = ((int)(pk & 0xffff) << lnw) + lane;
+                const uint32_t s0 = ((const uint8_t*)latp)[waddr];
+                const uint32_t n0 = lat[(D.y & 0xffff) << lnw], n1 = lat[(D.y >> 16) << lnw];
+                const uint32_t n2 = lat[(D.z & 0xffff) << lnw], n3 = lat[(D.z >> 16) << lnw];
+                int nv = (int)s0 + 1 + (int)(pk >> 16);
+                nv = nv >= q ? nv - q : nv;
+                pold = (uint8_t)s0;
                 pnew = (uint8_t)nv;
-                const int nold = (n0 == s0) + (n1 == s0) + (n2 == s0) + (n3 == s0);
-                const int nnew = (n0 == nv) + (n1 == nv) + (n2 == nv) + (n3 == nv);
-                nb = b + nold - nnew;                            // dE = n(old) - n(new)
+                const uint32_t n = n0 | (n1 << 8) | (n2 << 16) | (n3 << 24);
+                nb = b + bytes_unlike(n, (uint32_t)nv) - bytes_unlike(n, s0);   // dE = n(old) - n(new)
             }
             const double bn = lbase[nb];
             const uint32_t hn = lH[(nb << lnw) + lane];
             const double lngn = __builtin_fma((double)hn, scale, bn);   // +inf in a pad
             const double delta = lngc - lngn;                    // exact (or -inf)
-            // delta > vb accepts for certain; below vb - 2 band rejects for certain
-            bool f = delta > vb;
-            const bool band = !f && delta >= vb - band2;
-            if (__builtin_expect(__any(band), 0)) {
-                if (band) {
-                    f = slow_decide(I, T0 + (uint64_t)j, (uint32_t)slot, delta);
-                    atomicAdd((unsigned long long*)&I.ctr->slow, 1ull);
+            // above hi accepts for certain, below its lower bound rejects for certain
+            const float df = (float)delta;
+            bool f = df > hi;
+            const bool open = !f && df >= lower_of(hi, e32);
+            if (__builtin_expect(__any(open), 0)) {
+                if (open) {
+                    const int r = decide_draw(I, T0 + (uint64_t)j, (uint32_t)slot, delta);
+                    f = r & 1;
+                    if (r & 2) atomicAdd((unsigned long long*)&I.ctr->slow, 1ull);
                 }
             }
-            if (f) {
-                if (MODEL == 0) ((uint64_t*)latp)[waddr] = wnew;
-                else ((uint8_t*)latp)[waddr] = pnew;
-            }
+            // written either way: a store under a mask of its own costs a branch
+            if (MODEL == 0) ((uint64_t*)latp)[waddr] = f ? wnew : wold;
+            else ((uint8_t*)latp)[waddr] = f ? pnew : pold;
             b = f ? nb : b;
             hc = (f ? hn : hc) + inc;
             lH[(b << lnw) + lane] = hc;
             lngc = (f ? lngn : lngc) + incv;                     // exact: base + 2^-k H
         };
 
-        // the walker's draws arrive in register chunks of kChunk attempts; the
-        // next chunk's vector loads are in flight while this one is walked
-        constexpr int kChunk = 16;
-        const v4u* pkp = (const v4u*)(I.rpack + (size_t)slot * I.XP);
-        const v2d* vp = (const v2d*)(I.rv + (size_t)slot * I.XP);
-        v4u PA[kChunk / 4], PB[kChunk / 4];
-        v2d VA[kChunk / 2], VB[kChunk / 2];
-        auto load = [&](v4u* P, v2d* V, int64_t j0) {
+        for (uint32_t c = 0; c < nchunk; ++c) {
+            if (active) {
+                const Draw* r = ring + (size_t)(c & 1) * kDraws * nw + lane;
+                Draw D[kDraws];
 #pragma unroll
-            for (int i = 0; i < kChunk / 4; ++i) P[i] = gload(pkp + j0 / 4 + i);
+                for (int i = 0; i < kDraws; ++i) D[i] = r[i << lnw];
+                const uint32_t j0 = c * kDraws;
+                if (j0 + kDraws <= X) {
 #pragma unroll
-            for (int i = 0; i < kChunk / 2; ++i) V[i] = gload(vp + j0 / 2 + i);
-        };
-        auto walk = [&](const v4u* P, const v2d* V, int64_t j0, bool check) {
+                    for (int i = 0; i < kDraws; ++i) attempt(D[i], j0 + i);
+                } else {
 #pragma unroll
-            for (int i = 0; i < kChunk; ++i) {
-                if (!check || j0 + i < X) {
-                    const v4u q4 = P[i / 4];
-                    const uint32_t pk = (i & 3) == 0 ? q4.x : (i & 3) == 1 ? q4.y : (i & 3) == 2 ? q4.z : q4.w;
-                    const double vb = (i & 1) ? V[i / 2].y : V[i / 2].x;
-                    attempt(pk, vb, j0 + i);
+                    for (int i = 0; i < kDraws; ++i)
+                        if (j0 + i < X) attempt(D[i], j0 + i);
                 }
             }
-        };
-        // XP is a multiple of 2 kChunk, so every chunk load below stays inside the row
-        load(PA, VA, 0);
-        for (int64_t j0 = 0; j0 < X; j0 += 2 * kChunk) {
-            load(PB, VB, j0 + kChunk);
-            if (j0 + 2 * kChunk <= X) {
-                walk(PA, VA, j0, false);
-                if (j0 + 2 * kChunk < X) load(PA, VA, j0 + 2 * kChunk);
-                walk(PB, VB, j0 + kChunk, false);
-            } else {
-                walk(PA, VA, j0, true);
-                walk(PB, VB, j0 + kChunk, true);
-            }
+            __syncthreads();
         }
-        I.bin[slot] = b - kPad + lo;
-        I.swaps[slot] = -1;
+        if (active) {
+            I.bin[slot] = b - kPad + lo;
+            I.swaps[slot] = -1;
+        }
     }
-    __syncthreads();
 
     // ---- write back (absolute counts: the walker's offset added back)
     for (int l = 0; l < nw; ++l) {
         const uint64_t cl = rl64(cw, l);
-        for (int bb = lane; bb < WB; bb += nthr) {
+        for (int bb = tid; bb < WB; bb += nthr) {
             const uint32_t hv = lH[((bb + kPad) << lnw) + l];
             I.H[(size_t)(slot0 + l) * WB + bb] = hv == 0xffffffffu ? 0ull : (uint64_t)hv + cl;
         }
@@ -351,16 +311,16 @@ __device__ void sweep_tile(const Inst& I, const Tile& tile, char* smem)
         const uint64_t* lat = (const uint64_t*)latp;
         const int nwords = L * WPR;
         for (int l = 0; l < nw; ++l)
-            for (int w = lane; w < nwords; w += nthr) I.lat[(size_t)(slot0 + l) * nwords + w] = lat[(w << lnw) + l];
+            for (int w = tid; w < nwords; w += nthr) I.lat[(size_t)(slot0 + l) * nwords + w] = lat[(w << lnw) + l];
     } else {
         const uint8_t* lat = (const uint8_t*)latp;
         for (int l = 0; l < nw; ++l)
-            for (int w = lane; w < N; w += nthr) I.plat[(size_t)(slot0 + l) * N + w] = lat[(w << lnw) + l];
+            for (int w = tid; w < N; w += nthr) I.plat[(size_t)(slot0 + l) * N + w] = lat[(w << lnw) + l];
     }
 
     // ---- flatness of each walker (Sec. II.A, or Eq. (8)) over the levels of the
     //      window that occur; latched until the window merges
-    if (inc && lane < nw) {
+    if (inc && walks && lane < nw) {
         uint32_t mn = 0xffffffffu;
         uint64_t sum = 0;
         for (int bb = kPad; bb < WB + kPad; ++bb) {
@@ -386,7 +346,7 @@ __device__ __forceinline__ void sweep_one_tile(const Inst* __restrict__ insts, c
     }
 }
 
-__global__ void __launch_bounds__(64) k_sweep(const Inst* __restrict__ insts,
+__global__ void __launch_bounds__(128) k_sweep(const Inst* __restrict__ insts,
                                               const Tile* __restrict__ tiles, int ntiles)
 {
     extern __shared__ __align__(16) char smem[];
@@ -397,7 +357,7 @@ __global__ void __launch_bounds__(64) k_sweep(const Inst* __restrict__ insts,
 // takes the next tile from a queue counter until the tiles run out (the tiles
 // are ordered longest-first by the host).  The counter is reset by k_advance at
 // the end of the interval, so the launch sequence needs no memset.
-__global__ void __launch_bounds__(64) k_sweep_persist(const Inst* __restrict__ insts,
+__global__ void __launch_bounds__(128) k_sweep_persist(const Inst* __restrict__ insts,
                                                       const Tile* __restrict__ tiles, int ntiles,
                                                       int32_t* __restrict__ queue)
 {
@@ -675,7 +635,7 @@ __device__ void sweep_wave(const Inst& I, const Tile& tile, char* smem)
         // ---- lanes: draws and sites of the chunk's attempts
         const u32x4 x = draw(I.k0, I.k1, T0 + (uint64_t)(j0 + lane), (uint32_t)slot, kTagFlip);
         const int site = (int)(((uint64_t)x.x * (uint32_t)N) >> 32);
-        int rr = (int)((float)site * rL);          // site / L, at most one off (as in k_rng)
+        int rr = (int)((float)site * rL);          // site / L, at most one off, corrected below
         int cc = site - (int)__umul24((uint32_t)rr, (uint32_t)L);
         if (cc < 0) { --rr; cc += L; }
         else if (cc >= L) { ++rr; cc -= L; }

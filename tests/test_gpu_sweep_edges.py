@@ -1,0 +1,62 @@
+"""The sweeps at the sizes where their inner structure could go wrong, against the
+CPU oracle, bit for bit (integer state and ln g): intervals around the draw
+chunks (4, 8 and 64 attempts), proposed states above 127 (byte comparisons), odd
+and two-word rows, lattices smaller than a chunk (nearly every attempt is evaluated
+again), and tables so steep that a walker leaves the range of the FP32 differences
+at every other move, with every decision near its threshold taken exactly."""
+import numpy as np
+import pytest
+
+import oracle as O
+from test_gpu_parity import _tune, assert_same, rw  # noqa: F401  (rw: fixture)
+
+pytestmark = pytest.mark.gpu
+
+KINDS = ["lane", "lane-persist", "wave", "wave-device", "wave-map64"]
+
+
+def lockstep(rw, kw, tune, calls, table=None):
+    gpu, orc = rw.Rewl([rw.make_config(**kw)], tune=tune), O.Sim(O.make_config(**kw), init_lng=table)
+    try:
+        if table is not None:
+            gpu.set_initial_lng(table)
+        for n in calls:
+            gpu.run(n)
+            orc.run(n)
+            assert_same(gpu.state(), orc.state(), f"{kw} after {orc.t} intervals")
+        return gpu.stats()
+    finally:
+        gpu.close()
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("X", [1, 3, 4, 5, 7, 8, 9, 63, 64, 65, 130])
+def test_intervals_around_the_chunks(rw, kind, X):
+    for kw in (dict(model="ising", L=6, n_windows=2, m=2), dict(model="potts", q=5, L=7, n_windows=2, m=4)):
+        lockstep(rw, dict(kw, kfinal=12, X=X, seed=300 + X), _tune(rw, kind), (1, 2, 20))
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("kw", [dict(model="potts", q=200, L=9, n_windows=3, m=2), dict(model="potts", q=129, L=4, n_windows=1, m=2),
+                                dict(model="ising", L=126, n_windows=8, m=1), dict(model="ising", L=66, n_windows=4, m=2),
+                                dict(model="potts", q=3, L=65, n_windows=8, m=1), dict(model="ising", L=4, n_windows=1, m=64)],
+                         ids=lambda kw: f"{kw['model']}{kw.get('q', 2)}-L{kw['L']}")
+def test_shapes(rw, kind, kw):
+    lockstep(rw, dict(kw, kfinal=12, X=1500, seed=411), _tune(rw, kind), (1, 3))
+
+
+@pytest.mark.parametrize("kind", ["lane", "wave", "wave-device"])
+@pytest.mark.parametrize("slope", [0.0, 7.0, 300.0])
+@pytest.mark.parametrize("band", [0, -2])
+def test_steep_tables_and_wide_band(rw, kind, slope, band):
+    """ln g rising and falling by `slope` per bin (zigzag), at ln f = 1 and 2^-12."""
+    t = _tune(rw, kind)
+    t.guard_band_log2 = band
+    for kw in (dict(model="ising", L=12, n_windows=2, m=2), dict(model="potts", q=10, L=10, n_windows=2, m=2)):
+        N = kw["L"] ** 2
+        W = N + 1 if kw["model"] == "ising" else 2 * N + 1
+        table = slope * np.abs((np.arange(W) % 40) - 20.0)
+        for k0 in (0, 12):
+            st = lockstep(rw, dict(kw, k0=k0, kfinal=30, X=2000, seed=511), t, (1, 4), table)
+            if band and slope == 0.0:
+                assert st["slow_decisions"] > 0
