@@ -318,17 +318,23 @@ def rewl_set_timing(h, on: bool) -> None:
     _check(_lib.rewl_set_timing(h, 1 if on else 0), "rewl_set_timing")
 
 
+_new_bytes = ctypes.pythonapi.PyBytes_FromStringAndSize      # (None, n): n bytes, not yet written
+_new_bytes.argtypes = [ctypes.c_char_p, ctypes.c_ssize_t]
+_new_bytes.restype = ctypes.py_object
+
+
 def rewl_checkpoint(h) -> bytes:
     n = ctypes.c_size_t(0)
     _check(_lib.rewl_checkpoint(h, None, ctypes.byref(n)), "rewl_checkpoint")
-    buf = ctypes.create_string_buffer(n.value)
-    _check(_lib.rewl_checkpoint(h, buf, ctypes.byref(n)), "rewl_checkpoint")
-    return buf.raw[: n.value]
+    # the library writes into the bytes object itself: no cleared buffer, no second copy
+    blob = _new_bytes(None, n.value)
+    _check(_lib.rewl_checkpoint(h, ctypes.cast(ctypes.c_char_p(blob), _vp), ctypes.byref(n)), "rewl_checkpoint")
+    return blob
 
 
 def rewl_restore(h, blob: bytes) -> None:
-    buf = ctypes.create_string_buffer(blob, len(blob))
-    _check(_lib.rewl_restore(h, buf, len(blob)), "rewl_restore")
+    blob = bytes(blob)
+    _check(_lib.rewl_restore(h, ctypes.cast(ctypes.c_char_p(blob), _vp), len(blob)), "rewl_restore")
 
 
 def rewl_destroy(h) -> None:

@@ -1256,6 +1256,24 @@ __global__ void __launch_bounds__(256) k_concat(const Inst* __restrict__ insts, 
         out[b] = I.mask[b] ? out[b] + (target - lse) : -__builtin_inf();
 }
 
+// ---------------------------------------------------------------- collect
+// Up to kCollect pieces of device memory (16-byte aligned) into one buffer, a block each.
+constexpr int kCollect = 64;
+struct Collect {
+    const char* src[kCollect];
+    uint32_t off[kCollect], bytes[kCollect];   // off: a multiple of 16
+    int32_t n;
+};
+__global__ void __launch_bounds__(256) k_collect(const Collect c, char* __restrict__ out)
+{
+    const int p = blockIdx.x;
+    const uint32_t n16 = c.bytes[p] >> 4;
+    const uint4* s = (const uint4*)c.src[p];
+    uint4* o = (uint4*)(out + c.off[p]);
+    for (uint32_t i = threadIdx.x; i < n16; i += blockDim.x) o[i] = s[i];
+    for (uint32_t i = (n16 << 4) + threadIdx.x; i < c.bytes[p]; i += blockDim.x) out[c.off[p] + i] = c.src[p][i];
+}
+
 // ------------------------------------------------------ predicate probe
 // Evaluates the full acceptance predicate (fast test against log(u53 2^-53)
 // with the guard band, exact slow path inside it) on caller-given inputs.
