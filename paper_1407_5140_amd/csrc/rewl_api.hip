@@ -1249,29 +1249,27 @@ rewl_status rewl_thermo(int32_t model, int32_t L, const double* lng, int32_t S, 
     const int N = L * L, W = model == 0 ? N + 1 : 2 * N + 1;
     for (int t = 0; t < nT; ++t)
         if (!(T[t] > 0.0) || !std::isfinite(T[t])) return fail(REWL_E_INVALID, "temperatures must be finite and > 0");
-    for (int s = 0; s < S; ++s) {
-        bool any = false;
-        for (int b = 0; b < W; ++b) {
-            const double v = lng[(size_t)s * W + b];
-            if (std::isnan(v) || v == HUGE_VAL)
-                return fail(REWL_E_INVALID, "row " + std::to_string(s) + ": ln g holds NaN or +inf");
-            any |= v != -HUGE_VAL;
-        }
-        if (!any) return fail(REWL_E_INVALID, "row " + std::to_string(s) + ": no energy level occurs");
-    }
     const size_t in_b = (size_t)S * W * 8, out_b = (size_t)S * nT * 8;
-    DevBuf d_lng, d_T, d_u, d_c, d_f;
+    std::vector<int32_t> bad(S);
+    DevBuf d_lng, d_T, d_u, d_c, d_f, d_bad;
     HIP_TRY(d_lng.alloc(in_b));
     HIP_TRY(d_T.alloc((size_t)nT * 8));
     if (u) HIP_TRY(d_u.alloc(out_b));
     if (c) HIP_TRY(d_c.alloc(out_b));
     if (f) HIP_TRY(d_f.alloc(out_b));
+    HIP_TRY(d_bad.alloc((size_t)S * 4));
+    HIP_TRY(hipMemset(d_bad.p, 0, (size_t)S * 4));
     HIP_TRY(hipMemcpy(d_lng.p, lng, in_b, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(d_T.p, T, (size_t)nT * 8, hipMemcpyHostToDevice));
-    hipLaunchKernelGGL(k_thermo, dim3((nT + kThermoT - 1) / kThermoT, S), dim3(64), 0, 0,
-                       d_lng.as<double>(), W, model, N, d_T.as<double>(), nT, d_u.as<double>(),
-                       d_c.as<double>(), d_f.as<double>());
+    hipLaunchKernelGGL(k_thermo, dim3((nT + 15) / 16, (S + 15) / 16), dim3(512), 0, 0, d_lng.as<double>(), S, W, model, N,
+                       d_T.as<double>(), nT, d_bad.as<int32_t>(), d_u.as<double>(), d_c.as<double>(), d_f.as<double>());
     HIP_TRY(hipGetLastError());
+    // the first row that cannot be averaged, found by the kernel as it reads them
+    HIP_TRY(hipMemcpy(bad.data(), d_bad.p, (size_t)S * 4, hipMemcpyDeviceToHost));
+    for (int s = 0; s < S; ++s) {
+        if (bad[s] & kRowNan) return fail(REWL_E_INVALID, "row " + std::to_string(s) + ": ln g holds NaN or +inf");
+        if (bad[s]) return fail(REWL_E_INVALID, "row " + std::to_string(s) + ": no energy level occurs");
+    }
     if (u) HIP_TRY(hipMemcpy(u, d_u.p, out_b, hipMemcpyDeviceToHost));
     if (c) HIP_TRY(hipMemcpy(c, d_c.p, out_b, hipMemcpyDeviceToHost));
     if (f) HIP_TRY(hipMemcpy(f, d_f.p, out_b, hipMemcpyDeviceToHost));

@@ -162,3 +162,35 @@ def test_ensemble_full_size_potts_L100(rw):
     T = np.linspace(0.5, 3.0, 40)
     g = rw.rewl_thermo("potts", 100, orows, T)
     _assert_thermo(g, _oracle_thermo("potts", 100, orows, T))
+
+
+# Shapes at the edges of the tiles (16 rows, 16 temperatures, blocks of 64 levels, 8 waves),
+# grids narrow enough for the matrix path, wide ones, and one in no order.  Bounds as above.
+@pytest.mark.parametrize("rows,temps", [(1, 1), (2, 7), (15, 8), (16, 9), (17, 16), (33, 17), (5, 33)])
+@pytest.mark.parametrize("model,L", [("ising", 4), ("ising", 8), ("potts", 7), ("ising", 48), ("potts", 20)])
+def test_thermo_shapes(rw, model, L, rows, temps):
+    W = L * L + 1 if model == "ising" else 2 * L * L + 1
+    rng = np.random.default_rng(rows * 100 + temps)
+    x = np.linspace(-1, 1, W)
+    lg = L * L * 0.69 * (1 - x ** 2) + rng.normal(0, 0.3, (rows, W))
+    lg[:, rng.random(W) < 0.1] = -np.inf
+    if W > 400:
+        lg[0, 64:200] = -np.inf                                       # a whole block of absent levels
+    lg[-1, :-1] = -np.inf                                             # one level: u exact, c = 0
+    lg[-1, -1] = 1.0
+    for T in (np.linspace(1.9, 2.1, temps), np.geomspace(0.1, 50.0, temps), rng.permutation(np.linspace(0.7, 3.0, temps))):
+        _assert_thermo(rw.rewl_thermo(model, L, lg, T), _oracle_thermo(model, L, list(lg), T))
+
+
+def test_thermo_names_the_first_bad_row(rw):
+    lg = np.zeros((40, 65))
+    for T in (np.linspace(2.0, 2.1, 20), np.geomspace(0.01, 50.0, 20)):
+        for value, what in ((np.nan, "row 17: ln g holds NaN or"), (np.inf, "row 17: ln g holds NaN or"), (-np.inf, "row 17: no energy level")):
+            bad = lg.copy()
+            bad[30, 3] = np.nan
+            if value == -np.inf:
+                bad[17] = value
+            else:
+                bad[17, 64] = value
+            with pytest.raises(rw.RewlError, match=what):
+                rw.rewl_thermo("ising", 8, bad, T)
