@@ -194,3 +194,38 @@ def test_thermo_names_the_first_bad_row(rw):
                 bad[17, 64] = value
             with pytest.raises(rw.RewlError, match=what):
                 rw.rewl_thermo("ising", 8, bad, T)
+
+
+@pytest.mark.parametrize("L,h,overlap", [(16, 2, (3, 4)), (16, 3, (1, 10)), (24, 9, (9, 10)), (32, 64, (7, 8)),
+                                         (32, 65, (9, 10)), (32, 66, (19, 20)), (40, 131, (29, 30))])
+def test_ensemble_joins_of_many_overlaps(rw, L, h, overlap):
+    """Overlaps many windows deep, so that a window's join often lies above where the next
+    one was found on its own; more windows than the lanes of a wave.  Joins exact."""
+    kws = [dict(model="ising", L=L, n_windows=h, overlap=overlap, m=1, kfinal=12, X=100, seed=s) for s in (1, 2, 3)]
+    c = O.make_config(**kws[0])
+    W, (lo, hi), mask = O.n_bins(c), O.layout(c), O.mask_rule(c)
+    rng = np.random.default_rng(h)
+    gpu = rw.Rewl([rw.make_config(**kw) for kw in kws])
+    runs = np.zeros((3, h, int((hi - lo).max()) + 1))
+    for j in range(3):
+        t = np.round((L * np.sin(np.pi * np.arange(W) / W) + rng.normal(0, 0.1, W)) * 2.0 ** 16) / 2.0 ** 16
+        gpu.set_initial_lng(t, j)
+        for a in range(h):
+            runs[j, a, : hi[a] - lo[a] + 1] = t[lo[a]: hi[a] + 1]
+    grows, gjoin = gpu.ensemble([0, 1, 2], R=12, seed=9)
+    gpu.close()
+    orows, ojoin = EN.ensemble(c, mask, runs, R=12, seed=9)
+    assert np.array_equal(gjoin, ojoin)
+    ok = mask > 0
+    assert np.max(np.abs(grows[:, ok] - orows[:, ok])) < 1e-9
+
+
+def test_ensemble_reports_an_overlap_without_a_join(rw):
+    # overlaps of one bin: no five-point stencil fits
+    kw = dict(model="ising", L=8, n_windows=4, overlap=(0, 1), m=1, kfinal=8, X=100)
+    gpu = rw.Rewl([rw.make_config(seed=s, **kw) for s in (1, 2)])
+    with pytest.raises(rw.RewlError, match="row 0: no valid join"):
+        gpu.ensemble([0, 1], R=2)
+    with pytest.raises(rw.RewlError, match="no valid join"):
+        gpu.concat(1)
+    gpu.close()
