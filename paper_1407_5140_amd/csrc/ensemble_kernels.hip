@@ -53,12 +53,13 @@ __global__ void __launch_bounds__(256) k_boot_mean(const double* const* __restri
 // largest block so far (so the variance loses little).  One block per tile, its 8
 // waves taking every 8th block of bins.  201 rows of 20 001 levels at 601
 // temperatures: 2.47 -> 1.03 ms, and c 9.7e-14 -> 2.9e-16 off the sums in 80 bits.
-// Tiles whose 1/T spread so far that K would leave e^+-kSpread take the levels one by
-// one (thermo_direct): one wave per row and 8 temperatures, pass 1 for the largest
-// exponent and its bin, pass 2 for the sums about that energy.  Terms below e^-745.2
-// of the largest are zero in double precision.
+// Tiles whose 1/T spread so far that K would leave e^+-kSpread are marked, and taken by a
+// second launch level by level (k_thermo_direct): one block per row and 8 temperatures,
+// pass 1 for the largest exponent and its bin, pass 2 for the sums about that energy.
+// Terms below e^-745.2 of the largest are zero in double precision.  Redone by the waves
+// of the contraction's own block instead, the marked tiles of 16 rows of 20 001 levels at
+// 300 temperatures of 0.3 to 5 made a call of 1.61 ms out of 0.62.
 constexpr double kSpread = 64.0;
-enum : int32_t { kRowNan = 1, kRowEmpty = 2 };
 constexpr int kThermoT = 8;
 
 __device__ __forceinline__ double wave_sum(double v)
@@ -68,29 +69,48 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-__device__ void thermo_direct(const double* __restrict__ row, int W, int model, int N, const double* __restrict__ T,
-                              int nt, int32_t* __restrict__ bad, double* __restrict__ u, double* __restrict__ c,
-                              double* __restrict__ f)
+// Grid (ceil(nT / 8), S).  redo: null for every tile, or k_thermo's mark per tile of 8.
+// A block's waves take every 64 waves-th bin; up to 8 of them while that leaves a wave 4
+// steps of 64 bins and the whole grid fits the device at once: each wave pays about 300
+// cross-lane steps for its sums (4 x 552 temperatures, 513 levels: 91 us a call with one
+// wave, 106 with 8; 20 001 levels: 432 and 207).
+constexpr int kDirectWaves = 8;
+inline int direct_threads(int S, int nT, int W)
 {
-    const int lane = threadIdx.x & 63;
-    bool nan = false, any = false;
+    int w = 1;
+    while (w < kDirectWaves && W >= 512 * w && (int64_t)S * ((nT + kThermoT - 1) / kThermoT) * w * 2 <= 8192) w *= 2;
+    return 64 * w;
+}
+__global__ void __launch_bounds__(64 * kDirectWaves) k_thermo_direct(const double* __restrict__ lng, int W, int model, int N,
+                                                                  const double* __restrict__ temp, int nT,
+                                                                  const uint8_t* __restrict__ redo,
+                                                                  double* __restrict__ u, double* __restrict__ c,
+                                                                  double* __restrict__ f)
+{
+    constexpr int n = kThermoT;
+    const int waves = blockDim.x >> 6;
+    const int t0 = blockIdx.x * n, s = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (redo && !redo[(size_t)s * gridDim.x + blockIdx.x]) return;
+    const double* T = temp + t0;
+    const double* row = lng + (size_t)s * W;
+    const int nt = nT - t0 < n ? nT - t0 : n;
     const double twoN = 2.0 * N;
-    double beta[kThermoT], mx[kThermoT];
-    int arg[kThermoT];
+    __shared__ double part[kDirectWaves][3][n];
+    __shared__ int at[kDirectWaves][n];
+    double beta[n], mx[n];
+    int arg[n];
 #pragma unroll
-    for (int i = 0; i < kThermoT; ++i) {
+    for (int i = 0; i < n; ++i) {
         beta[i] = 1.0 / T[i < nt ? i : nt - 1];
         mx[i] = -__builtin_inf();
         arg[i] = W;
     }
-    for (int b = lane; b < W; b += 64) {
+    for (int b = threadIdx.x; b < W; b += blockDim.x) {
         const double v = row[b];
-        nan |= v != v || v == __builtin_inf();
         if (!(v > -__builtin_inf())) continue;
-        any = true;
         const double E = model == 0 ? 4.0 * b - twoN : (double)b - twoN;
 #pragma unroll
-        for (int i = 0; i < kThermoT; ++i) {
+        for (int i = 0; i < n; ++i) {
             const double x = v - beta[i] * E;
             if (x > mx[i]) {
                 mx[i] = x;
@@ -98,14 +118,9 @@ __device__ void thermo_direct(const double* __restrict__ row, int W, int model, 
             }
         }
     }
-    if (nan) atomicOr(bad, kRowNan);
-    if (!__any(any)) {
-        if (lane == 0) atomicOr(bad, kRowEmpty);
-        return;
-    }
-    // wave max with the lowest bin on ties
+    // the maximum with the lowest bin on ties: over the wave, then over the waves
 #pragma unroll
-    for (int i = 0; i < kThermoT; ++i) {
+    for (int i = 0; i < n; ++i) {
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
             const double m2 = __shfl_xor(mx[i], o, 64);
@@ -115,19 +130,33 @@ __device__ void thermo_direct(const double* __restrict__ row, int W, int model, 
                 arg[i] = a2;
             }
         }
+        if (lane == 0) {
+            part[wave][0][i] = mx[i];
+            at[wave][i] = arg[i];
+        }
     }
-    double Em[kThermoT], Z[kThermoT], S1[kThermoT], S2[kThermoT];
+    __syncthreads();
+    double Em[n], Z[n], S1[n], S2[n];
 #pragma unroll
-    for (int i = 0; i < kThermoT; ++i) {
+    for (int i = 0; i < n; ++i) {
+        for (int w = 0; w < waves; ++w) {
+            const double m2 = part[w][0][i];
+            const int a2 = at[w][i];
+            if (m2 > mx[i] || (m2 == mx[i] && a2 < arg[i])) {
+                mx[i] = m2;
+                arg[i] = a2;
+            }
+        }
         Em[i] = model == 0 ? 4.0 * arg[i] - twoN : (double)arg[i] - twoN;
         Z[i] = S1[i] = S2[i] = 0.0;
     }
-    for (int b = lane; b < W; b += 64) {
+    __syncthreads();
+    for (int b = threadIdx.x; b < W; b += blockDim.x) {
         const double v = row[b];
         if (!(v > -__builtin_inf())) continue;
         const double E = model == 0 ? 4.0 * b - twoN : (double)b - twoN;
 #pragma unroll
-        for (int i = 0; i < kThermoT; ++i) {
+        for (int i = 0; i < n; ++i) {
             const double d = (v - beta[i] * E) - mx[i];
             if (d >= -745.2) {
                 const double w = exp(d), e = E - Em[i], we = w * e;
@@ -138,22 +167,34 @@ __device__ void thermo_direct(const double* __restrict__ row, int W, int model, 
         }
     }
 #pragma unroll
-    for (int i = 0; i < kThermoT; ++i) {
+    for (int i = 0; i < n; ++i) {
         Z[i] = wave_sum(Z[i]);
         S1[i] = wave_sum(S1[i]);
         S2[i] = wave_sum(S2[i]);
+        if (lane == 0) {
+            part[wave][0][i] = Z[i];
+            part[wave][1][i] = S1[i];
+            part[wave][2][i] = S2[i];
+        }
     }
-    if (lane < nt) {
+    __syncthreads();
+    if (threadIdx.x < nt) {
         double zz = 0, s1 = 0, s2 = 0, em = 0, m = 0;
 #pragma unroll
-        for (int i = 0; i < kThermoT; ++i)
+        for (int i = 0; i < n; ++i)
             if (i == lane) {
-                zz = Z[i]; s1 = S1[i]; s2 = S2[i]; em = Em[i]; m = mx[i];
+                em = Em[i]; m = mx[i];
             }
+        for (int w = 0; w < waves; ++w) {
+            zz += part[w][0][lane];
+            s1 += part[w][1][lane];
+            s2 += part[w][2][lane];
+        }
         const double t = T[lane], mean = s1 / zz;
-        if (u) u[lane] = (em + mean) / N;
-        if (c) c[lane] = (s2 / zz - mean * mean) / ((double)N * t * t);
-        if (f) f[lane] = -t * (m + log(zz)) / N;
+        const size_t o = (size_t)s * nT + t0 + lane;
+        if (u) u[o] = (em + mean) / N;
+        if (c) c[o] = (s2 / zz - mean * mean) / ((double)N * t * t);
+        if (f) f[o] = -t * (m + log(zz)) / N;
     }
 }
 
@@ -177,12 +218,11 @@ __device__ __forceinline__ void merge(Moments& a, const Moments& b)
     a.E0 = E0;
 }
 
-// Grid (ceil(nT / 16), ceil(S / 16)); bad[s] receives kRow* bits.
+// Grid (ceil(nT / 16), ceil(S / 16)); every row has a finite level and neither NaN nor +inf.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 __global__ void __launch_bounds__(512) k_thermo(const double* __restrict__ lng, int S, int W, int model, int N,
-                                                const double* __restrict__ T, int nT, int32_t* __restrict__ bad,
-                                                double* __restrict__ u, double* __restrict__ c,
-                                                double* __restrict__ f)
+                                                const double* __restrict__ T, int nT, uint8_t* __restrict__ redo, double* __restrict__ u,
+                                                double* __restrict__ c, double* __restrict__ f)
 {
     __shared__ double K[64][16];
     __shared__ Moments part[4][256];
@@ -196,13 +236,11 @@ __global__ void __launch_bounds__(512) k_thermo(const double* __restrict__ lng, 
         lo = l2 < lo ? l2 : lo;
         hi = h2 > hi ? h2 : hi;
     }
+    const int nt8 = (nT + kThermoT - 1) / kThermoT, mark = 2 * blockIdx.x + (tid & 1);
+    const size_t mine = (size_t)(s0 + (tid >> 1)) * nt8 + mark;
+    const bool marks = tid < 32 && s0 + (tid >> 1) < S && mark < nt8;
     if (!((hi - lo) * (16.0 * step) <= kSpread)) {           // block-uniform
-        for (int s = s0 + wave; s < S && s < s0 + 16; s += 8)
-            for (int t = 0; t < nt; t += kThermoT) {
-                const size_t o = (size_t)s * nT + t0 + t;
-                thermo_direct(lng + (size_t)s * W, W, model, N, T + t0 + t, nt - t < kThermoT ? nt - t : kThermoT, bad + s,
-                              u ? u + o : u, c ? c + o : c, f ? f + o : f);
-            }
+        if (marks) redo[mine] = 1;
         return;
     }
     const double mid = 0.5 * (lo + hi);
@@ -215,7 +253,6 @@ __global__ void __launch_bounds__(512) k_thermo(const double* __restrict__ lng, 
     Moments m[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) m[r] = {-__builtin_inf(), 0.0, 0.0, 0.0, 0.0, 0.0};
-    bool nan = false;
     for (int k = wave; k * 64 < W; k += 8) {
         // rows li, bins 4 q + lk of the block
         double a[16], top = -__builtin_inf();
@@ -223,14 +260,13 @@ __global__ void __launch_bounds__(512) k_thermo(const double* __restrict__ lng, 
         for (int q = 0; q < 16; ++q) {
             const int b = k * 64 + 4 * q + lk;
             a[q] = b < W ? row[b] : -__builtin_inf();
-            nan |= a[q] != a[q] || a[q] == __builtin_inf();
             top = a[q] > top ? a[q] : top;
         }
         for (int o = 16; o < 64; o <<= 1) {
             const double t2 = __shfl_xor(top, o);
             top = t2 > top ? t2 : top;
         }
-        const bool some = top > -__builtin_inf() && top < __builtin_inf();
+        const bool some = top > -__builtin_inf();
         double mx = -__builtin_inf();
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
@@ -256,7 +292,7 @@ __global__ void __launch_bounds__(512) k_thermo(const double* __restrict__ lng, 
         for (int r = 0; r < 4; ++r) {
             const double tp = __shfl(top, 4 * r + lk), mr = __shfl(mx, 4 * r + lk);
             Moments b = {-__builtin_inf(), 0.0, Ek, Z[r], S1[r], S2[r]};
-            if (tp > -__builtin_inf() && tp < __builtin_inf()) {
+            if (tp > -__builtin_inf()) {
                 const dd sum = two_sum(tp, -p);
                 b.hi = sum.hi;
                 b.lo = (sum.lo - pe) + mr;
@@ -264,7 +300,6 @@ __global__ void __launch_bounds__(512) k_thermo(const double* __restrict__ lng, 
             merge(m[r], b);
         }
     }
-    if (nan) atomicOr(&bad[srow], kRowNan);
     // the 8 waves' sums, pairwise
     for (int w = 4; w > 0; w >>= 1) {
         if (wave >= w && wave < 2 * w)
@@ -285,10 +320,6 @@ __global__ void __launch_bounds__(512) k_thermo(const double* __restrict__ lng, 
         for (int r = 0; r < 4; ++r) {
             const int s = s0 + 4 * r + lk;
             if (s >= S) continue;
-            if (m[r].hi == -__builtin_inf()) {
-                atomicOr(&bad[s], kRowEmpty);
-                continue;
-            }
             const double mean = m[r].S1 / m[r].Z, sq = m[r].S2 / m[r].Z, var = sq - mean * mean;
             const size_t o = (size_t)s * nT + t0 + li;
             if (u) u[o] = (m[r].E0 + mean) / N;
@@ -300,13 +331,7 @@ __global__ void __launch_bounds__(512) k_thermo(const double* __restrict__ lng, 
     __syncthreads();
     // a variance far below the distance to Ek squared (low temperatures: one level has
     // nearly all the weight) has lost digits: those again about the level itself
-    for (int e = wave; e < 32; e += 8) {
-        const int s = s0 + (e >> 1), t = (e & 1) * kThermoT;
-        if (!weak[e >> 1][e & 1]) continue;
-        const size_t o = (size_t)s * nT + t0 + t;
-        thermo_direct(lng + (size_t)s * W, W, model, N, T + t0 + t, nt - t < kThermoT ? nt - t : kThermoT, bad + s,
-                      u ? u + o : u, c ? c + o : c, f ? f + o : f);
-    }
+    if (marks) redo[mine] = (uint8_t)weak[tid >> 1][tid & 1];
 }
 
 }  // namespace rewl

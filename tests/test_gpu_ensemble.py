@@ -182,6 +182,24 @@ def test_thermo_shapes(rw, model, L, rows, temps):
         _assert_thermo(rw.rewl_thermo(model, L, lg, T), _oracle_thermo(model, L, list(lg), T))
 
 
+# The same on both sides of the 10 000 rows x temperatures from which the contraction is
+# used: part tiles of rows, of temperatures and of 8 in 16, one temperature, many waves.
+@pytest.mark.parametrize("rows,temps", [(99, 101), (100, 100), (17, 589), (10001, 1), (313, 33), (1, 10007)])
+@pytest.mark.parametrize("model,L", [("ising", 4), ("potts", 7), ("ising", 33)])
+def test_thermo_tiles(rw, model, L, rows, temps):
+    W = L * L + 1 if model == "ising" else 2 * L * L + 1
+    rng = np.random.default_rng(rows + temps)
+    x = np.linspace(-1, 1, W)
+    lg = L * L * 0.69 * (1 - x ** 2) + rng.normal(0, 0.3, (rows, W))
+    lg[:, rng.random(W) < 0.1] = -np.inf
+    lg[-1, :-1] = -np.inf
+    lg[-1, -1] = 1.0
+    some = sorted({0, rows // 2, rows - 2, rows - 1} - {-1})
+    for T in (np.linspace(1.9, 2.1, temps), np.geomspace(0.1, 50.0, temps), rng.permutation(np.linspace(0.7, 3.0, temps))):
+        g = rw.rewl_thermo(model, L, lg, T)
+        _assert_thermo(tuple(np.asarray(x)[some] for x in g), _oracle_thermo(model, L, [lg[i] for i in some], T))
+
+
 def test_thermo_names_the_first_bad_row(rw):
     lg = np.zeros((40, 65))
     for T in (np.linspace(2.0, 2.1, 20), np.geomspace(0.01, 50.0, 20)):
