@@ -84,12 +84,14 @@ typedef struct {
  *                   0 <= num, 1 <= den, both <= 2^20.                                */
 enum { REWL_FLAT_MEAN = 0, REWL_FLAT_VISITS = 1 };
 
-/* Sweep variants.  LANE: one walker per lane, draws precomputed for the whole
- * interval by a separate kernel (suits batches of many thousands of walkers).
+/* Sweep variants.  LANE: one walker per lane, the draws made meanwhile by a second
+ * wave of the block (suits many thousands of walkers on small lattices).
  * WAVE: one walker per wave, the chain on wave-uniform values, the lanes draw
- * the next 64 attempts (suits few walkers; falls back to LANE where one walker's
- * wave tables do not fit the LDS).  AUTO: WAVE for a batch of at most 8192
- * walkers in all, LANE above that.  Both give bit-identical results.            */
+ * the next 64 attempts (suits few walkers and large lattices; falls back to LANE
+ * where one walker's wave tables do not fit the LDS).  AUTO: WAVE, but LANE (as a
+ * persistent grid, tiles of at most 40 KB unless lds_target_kb says otherwise) for
+ * the instances whose LANE tables take at most 1.75 KB per walker if those have
+ * 16384 walkers or more in all.  Both give bit-identical results.                */
 enum { REWL_SWEEP_AUTO = 0, REWL_SWEEP_LANE = 1, REWL_SWEEP_WAVE = 2 };
 
 /* Where the WAVE sweep keeps a walker's counts while it runs.  LDS: a 32-bit copy

@@ -159,6 +159,7 @@ struct rewl_handle {
     Tile* d_tiles = nullptr;
     int ntiles = 0;
     int32_t* d_queue = nullptr; // tile queue of the persistent lane sweep
+    bool persist = false;       // asked for, or the library's own choice of variant
     int persist_grid = 0;       // its blocks: as many as the GPU holds at once
     Tile* d_wtiles = nullptr;
     int nwtiles = 0;
@@ -249,7 +250,7 @@ rewl_status enqueue_interval(rewl_handle* H, bool time_it)
 {
     if (time_it) HIP_TRY(hipEventRecord(H->ev[0], H->stream));
     if (time_it) HIP_TRY(hipEventRecord(H->ev[1], H->stream));
-    if (H->ntiles > 0 && H->tune.persistent)
+    if (H->ntiles > 0 && H->persist)
         hipLaunchKernelGGL(k_sweep_persist, dim3(H->persist_grid), dim3(128), H->max_lds, H->stream, H->d_insts,
                            H->d_tiles, H->ntiles, H->d_queue);
     else if (H->ntiles > 0)
@@ -646,6 +647,7 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
     H->device = dev;
     if (tune) H->tune = *tune;
     if (H->tune.poll_every <= 0) H->tune.poll_every = 8;
+    H->persist = H->tune.persistent || H->tune.sweep_kind == REWL_SWEEP_AUTO;
     const double band = H->tune.guard_band_log2 ? std::ldexp(1.0, H->tune.guard_band_log2) : kBand;
     H->n = n;
     H->inst.resize(n);
@@ -667,6 +669,33 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
     for (int k = 0; k < 4; ++k)
         if (hipEventCreate(&H->ev[k]) != hipSuccess) return bail(fail(REWL_E_DEVICE, "hipEventCreate failed"));
 
+    // AUTO's choice between the variants, per instance.  The wave variant makes about 6
+    // walkers' intervals of 10^4 attempts per us whatever the lattice; the lane variant is
+    // limited by the walkers whose tables the LDS holds at once (about 0.03 + 0.075 us per
+    // KB of a walker's tables), and an interval takes it 2.9 ms however few they are.  So
+    // it takes the instances of small tables where there are enough of them.  Measured,
+    // ms per interval, lane against wave: Ising L=16, 131 072 walkers (0.7 KB) 9.0 / 25.9,
+    // 16 384 walkers 2.7 / 3.5; Potts q=10 L=16, 131 072 (1.2 KB) 12.9 / 22.0; Ising L=64,
+    // 32 768 (2.5 KB) 6.8 / 5.5; Potts q=10 L=32, 32 768 (2.8 KB) 8.1 / 4.8; 64 unequal
+    // instances, 65 280 walkers: all lane 11.2, all wave 11.4, by this rule 10.8.
+    // Its lane tiles are capped at 40 KB (Ising L=16, 131 072 walkers: 10.3 at 53 KB, 8.9)
+    // and handed out by the queue (11.5 to 10.2 there).
+    constexpr size_t kLaneBytes = 1792, kLaneTile = size_t(40) << 10;
+    constexpr int64_t kLaneWalkers = 16384;
+    int64_t total_walkers = 0, small_walkers = 0;
+    std::vector<size_t> lane_bytes(n);
+    for (int u = 0; u < n; ++u) {
+        const rewl_config& c = cfgs[u];
+        const int64_t S = (int64_t)c.n_windows * c.walkers_per_window;
+        std::vector<int32_t> lo, hi;
+        layout_of(c, lo, hi);
+        int WB = 0;
+        for (int a = 0; a < c.n_windows; ++a) WB = std::max(WB, hi[a] - lo[a] + 1);
+        lane_bytes[u] = sweep_lds_bytes(c.model, c.L, c.model == 0 ? (c.L + 63) / 64 : 1, WB, 32) / 32;
+        total_walkers += S;
+        if (lane_bytes[u] <= kLaneBytes) small_walkers += S;
+    }
+    const bool many_small = small_walkers >= kLaneWalkers;
     for (int i = 0; i < n; ++i) {
         HostInst& hi = H->inst[i];
         hi.cfg = cfgs[i];
@@ -685,24 +714,16 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
         hi.nreach.assign(hi.h, 0);
         for (int a = 0; a < hi.h; ++a)
             for (int b = hi.lo[a]; b <= hi.hi[a]; ++b) hi.nreach[a] += hi.mask[b];
-        // sweep variant.  The lane variant serves a wave of walkers with ~74
-        // instructions per wave-attempt; the wave variant serves one walker with
-        // ~27 per attempt (chunked evaluation and runs).  With few walkers per
-        // SIMD the chain latency sets the rate and the wave variant wins (about
-        // 2.4x on Ising L=64 with 1024 walkers and on Potts q=10 L=32 with 4096);
-        // with tens of thousands of walkers the lane variant's width wins (the
-        // 64-instance batch).  The wave variant takes any lattice whose walker
-        // tables fit the LDS with the smallest site map the choice below may
-        // take, or with the one asked for.
+        // sweep variant.  The wave variant takes any lattice whose walker tables fit the
+        // LDS with the smallest site map the choice below may take, or with the one
+        // asked for.
         const bool wave_ok =
             wave_lds_bytes(c.model, c.L, hi.WB, 1, true,
                            wave_map_entries(hi.N, H->tune.map_log2 > 0 ? H->tune.map_log2 : 9)) <=
             (size_t)lds_limit;
-        int64_t total_walkers = 0;
-        for (int u = 0; u < n; ++u) total_walkers += (int64_t)cfgs[u].n_windows * cfgs[u].walkers_per_window;
         hi.kind = REWL_SWEEP_LANE;
         if (wave_ok && (H->tune.sweep_kind == REWL_SWEEP_WAVE ||
-                        (H->tune.sweep_kind == REWL_SWEEP_AUTO && total_walkers <= 8192)))
+                        (H->tune.sweep_kind == REWL_SWEEP_AUTO && !(many_small && lane_bytes[i] <= kLaneBytes))))
             hi.kind = REWL_SWEEP_WAVE;
         hi.placement = REWL_TABLE_LDS;
         if (hi.kind == REWL_SWEEP_LANE) {
@@ -711,13 +732,14 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
             while (wpb * 2 <= std::min(want, std::min(64, hi.m))) wpb *= 2;
             size_t cap = (size_t)lds_limit;
             if (H->tune.lds_target_kb > 0) cap = std::min(cap, (size_t)H->tune.lds_target_kb * 1024);
+            else if (H->tune.sweep_kind == REWL_SWEEP_AUTO) cap = std::min(cap, kLaneTile);
             while (wpb > 1 && sweep_lds_bytes(c.model, c.L, hi.wpr, hi.WB, wpb) > cap) wpb /= 2;
             hi.wpb = wpb;
             hi.lds = sweep_lds_bytes(c.model, c.L, hi.wpr, hi.WB, wpb);
             H->max_lds = std::max(H->max_lds, hi.lds);
         } else {
             WavePlan best;
-            if (!plan_wave(c.model, c.L, hi.N, hi.WB, hi.m, hi.S, H->tune, lds_limit, n_cu, wave_cap, &best))
+            if (!plan_wave(c.model, c.L, hi.N, hi.WB, hi.m, total_walkers, H->tune, lds_limit, n_cu, wave_cap, &best))
                 return bail(fail(REWL_E_INVALID, "instance " + std::to_string(i) + ": one walker's tables exceed LDS"));
             hi.placement = best.hg ? REWL_TABLE_DEVICE : REWL_TABLE_LDS;
             hi.wpb = best.G;
@@ -906,6 +928,11 @@ static rewl_status autotune(const rewl_config* cfgs, int32_t n, void* hip_stream
             t.autotune = 0;
             cand.push_back(t);
         }
+    rewl_tune mixed = base;             // the library's own choice, instance by instance
+    mixed.sweep_kind = REWL_SWEEP_AUTO;
+    mixed.walkers_per_block = mixed.lds_target_kb = mixed.map_log2 = mixed.autotune = 0;
+    mixed.table_placement = REWL_TABLE_AUTO;
+    cand.push_back(mixed);
     double best_ms = 1e300;
     *best = cand[0];
     for (const rewl_tune& t : cand) {

@@ -60,3 +60,22 @@ def test_steep_tables_and_wide_band(rw, kind, slope, band):
             st = lockstep(rw, dict(kw, k0=k0, kfinal=30, X=2000, seed=511), t, (1, 4), table)
             if band and slope == 0.0:
                 assert st["slow_decisions"] > 0
+
+
+@pytest.mark.parametrize("small,lanes", [(31, False), (32, True)])
+def test_auto_splits_a_batch(rw, small, lanes):
+    """15 872 and 16 384 walkers of small tables beside a larger lattice: the variant per
+    instance, and the same states as with either variant for all."""
+    kws = [dict(model="ising", L=6, n_windows=2, m=256, kfinal=12, X=70, seed=s) for s in range(small)]
+    kws.insert(3, dict(model="potts", q=10, L=32, n_windows=3, m=2, kfinal=12, X=70, seed=99))
+    states = []
+    for kind in ("auto", "lane", "wave"):
+        gpu = rw.Rewl([rw.make_config(**kw) for kw in kws], tune=rw.make_tune(kind))
+        if kind == "auto":
+            assert [gpu.info(i)["sweep_kind"] for i in (0, 3, small)] == (["lane", "wave", "lane"] if lanes else ["wave"] * 3)
+        gpu.run(5)
+        states.append([gpu.state(i) for i in (0, 3, small)])
+        gpu.close()
+    for other in states[1:]:
+        for a, b in zip(states[0], other):
+            assert_same(a, b, f"{small} small instances")
