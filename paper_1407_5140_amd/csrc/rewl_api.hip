@@ -928,11 +928,6 @@ static rewl_status autotune(const rewl_config* cfgs, int32_t n, void* hip_stream
             t.autotune = 0;
             cand.push_back(t);
         }
-    rewl_tune mixed = base;             // the library's own choice, instance by instance
-    mixed.sweep_kind = REWL_SWEEP_AUTO;
-    mixed.walkers_per_block = mixed.lds_target_kb = mixed.map_log2 = mixed.autotune = 0;
-    mixed.table_placement = REWL_TABLE_AUTO;
-    cand.push_back(mixed);
     double best_ms = 1e300;
     *best = cand[0];
     for (const rewl_tune& t : cand) {
