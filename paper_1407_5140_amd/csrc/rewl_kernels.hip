@@ -417,19 +417,19 @@ __device__ __forceinline__ uint32_t first_bit(uint64_t m)
     return r;
 }
 
-// c if the wave-uniform masks a and b are equal, else 0 (kept on the scalar side).
-__device__ __forceinline__ uint64_t equal_then(uint64_t a, uint64_t b, uint64_t c)
+// c if bit i (modulo 64) of the wave-uniform mask m is set, else 0.
+__device__ __forceinline__ uint32_t bit_then(uint64_t m, uint32_t i, uint32_t c)
 {
-    uint64_t r;
-    asm("s_cmp_eq_u64 %1, %2\n\ts_cselect_b64 %0, %3, 0" : "=s"(r) : "s"(a), "s"(b), "s"(c) : "scc");
+    uint32_t r;
+    asm("s_bitcmp1_b64 %1, %2\n\ts_cselect_b32 %0, %3, 0" : "=s"(r) : "s"(m), "s"(i), "s"(c) : "scc");
     return r;
 }
 
-// c if bit i of the wave-uniform mask m is set, else 0.
-__device__ __forceinline__ uint64_t bit_then(uint64_t m, int i, uint64_t c)
+// a if bit i (modulo 64) of the wave-uniform mask m is set, else b.
+__device__ __forceinline__ uint32_t bit_pick(uint64_t m, uint32_t i, uint32_t a, uint32_t b)
 {
-    uint64_t r;
-    asm("s_bitcmp1_b64 %1, %2\n\ts_cselect_b64 %0, %3, 0" : "=s"(r) : "s"(m), "s"(i), "s"(c) : "scc");
+    uint32_t r;
+    asm("s_bitcmp1_b64 %1, %2\n\ts_cselect_b32 %0, %3, %4" : "=s"(r) : "s"(m), "s"(i), "s"(a), "s"(b) : "scc");
     return r;
 }
 
@@ -489,6 +489,14 @@ __device__ __forceinline__ int ising_d_words(const uint64_t* rows, int wpr, int 
 // stored and by the flatness test, so LDS then holds only the window's base table,
 // the site maps and the lattices, and more walkers fit a block.  Both placements
 // compute identical results.
+// A walker alone on its SIMD is bound by the issue of its own instructions and the
+// hand-overs between the lanes and the scalar side, not by memory or arithmetic: a step is
+// 28 instructions and about 195 cycles, a round's start and end 600, a chunk's draws and
+// sets 600 (Ising L=64, middle windows: 26 steps and 2.2 rounds per chunk).  A step in
+// FP64 on exact values took 390 cycles, one of 34 instructions 270.  Interval of 10^4
+// attempts, us, with FP64 steps / 34 instructions / now: Ising L=32, 128 walkers 1090 / 695
+// / 545; L=64, 1024: 1100 / 656 / 512; L=128, 2048: 1249 / 811 / 690; Potts q=10 L=32, 4096
+// (4 to a SIMD): 1699 / 970 / 842; L=64, 4096: 1725 / 1180 / 984.
 template <int MODEL, bool WIDE, bool HG>
 __device__ void sweep_wave(const Inst& I, const Tile& tile, char* smem)
 {
@@ -597,32 +605,33 @@ __device__ void sweep_wave(const Inst& I, const Tile& tile, char* smem)
     // The steps compare in FP32: g0 = ln g of each bin of the window less that of
     // the bin the walker was in when it was taken, gl holding the exact values of
     // that moment; cnt = visits since then of the bins that the walker has left,
-    // cur = g0 + cnt 2^-k.  The walker came to its bin at attempt je of the chunk,
-    // and lb + j 2^-k is its ln g there before attempt j.  The walker may step to
-    // the bins of `safe`, whose g0 is below 64, away from the window's edge; when it
-    // leaves them, and at the end of a chunk, the visits go into gl (exact) and g0 is
-    // taken afresh.  Every quantity that a decision can depend on then stays below
-    // 512, the seven roundings on its way (six of at most 2^-16) below kErr32, and an
-    // attempt closer to its threshold than that is decided on the exact values.
+    // cur = g0 + cnt 2^-k.  The walker's own bin (hot = 1) has in cnt less the attempt
+    // of the chunk at which the walker came, and lb + j 2^-k is its ln g before
+    // attempt j.  The walker may step to the bins of `safe`, whose g0 is below 64, away
+    // from the window's edge; when it leaves them, and at the end of a chunk, the visits
+    // go into gl (exact) and g0 is taken afresh.  Every quantity that a decision can
+    // depend on then stays below 512, the seven roundings on its way (six of at most
+    // 2^-16) below kErr32, and an attempt closer to its threshold than that is decided
+    // on the exact values.
     constexpr float kErr32 = 0x1p-13f;
     const float inc32 = (float)incv, laneinc = (float)lane * inc32;       // exact
-    float g0, cur, cnt = 0.0f, je = 0.0f, lb;
+    float g0, cur, cnt = 0.0f, hot = lane == idx ? 1.0f : 0.0f, lb;
     uint64_t safe;
     auto settle = [&](int j) {            // attempts below j of the chunk are decided
-        cnt += lane == idx ? (float)j - je : 0.0f;
+        cnt = __builtin_fmaf((float)j, hot, cnt);
         gl = __builtin_fma((double)cnt, incv, gl);            // exact
-        cnt = 0.0f;
         if (__builtin_expect((unsigned)(idx - 4) > 55u, 0)) { // idx < 4 or idx > 59
             store_window();                                   // move the window around the walker
             const int bb = b0 + idx;
             b0 = bb - 32 < 0 ? 0 : (bb - 32 > b0max ? b0max : bb - 32);
             idx = bb - b0;
             load_window();
+            hot = lane == idx ? 1.0f : 0.0f;
         }
         cur = g0 = (float)(gl - rld(gl, idx));
         safe = __builtin_amdgcn_ballot_w64(__builtin_fabsf(g0) < 64.0f) & 0x0ffffffffffffff0ull;
-        je = (float)j;
-        lb = -je * inc32;
+        cnt = -(float)j * hot;
+        lb = -(float)j * inc32;
     };
     settle(0);
     const float rL = 1.0f / (float)L;
@@ -637,34 +646,36 @@ __device__ void sweep_wave(const Inst& I, const Tile& tile, char* smem)
         const int site = (int)(((uint64_t)x.x * (uint32_t)N) >> 32);
         int rr = (int)((float)site * rL);          // site / L, at most one off, corrected below
         int cc = site - (int)__umul24((uint32_t)rr, (uint32_t)L);
-        if (cc < 0) { --rr; cc += L; }
-        else if (cc >= L) { ++rr; cc -= L; }
+        const int fix = cc < 0 ? -1 : (cc >= L ? 1 : 0);
+        rr += fix;
+        cc -= fix * L;
         const bool top = rr == 0, bottom = rr == L - 1;
         const int ru = top ? L - 1 : rr - 1, rd = bottom ? 0 : rr + 1;
         const int s_up = top ? site + (N - L) : site - L, s_dn = bottom ? site - (N - L) : site + L;
         const int s_lf = cc == 0 ? site + (L - 1) : site - 1, s_rt = cc == L - 1 ? site - (L - 1) : site + 1;
-        const uint32_t off = MODEL == 0 ? 0u : (uint32_t)(((uint64_t)x.y * qm1) >> 32);
-        // bounds of the acceptance threshold less the lane's updates: with y = lb minus
-        // cur of the candidate bin, y > whi accepts and y < wlo rejects for certain
-        const Bound32 tb = bounds_of(x.z, x.w, band32);
-        const float whi = tb.hi - laneinc, wlo = tb.lo - laneinc;
         // attempts of the chunk at this attempt's site or one of its neighbours.
         // Neighbourhoods are symmetric, so the later ones among them (qm) are
         // exactly the attempts whose evaluation a flip of this one makes out of
         // date, and the earlier ones (pm) those whose flip makes this one out of
         // date.  (Sites sharing a map entry only add attempts to either set.)
-        if (lane < n) atomicOr((unsigned long long*)&lmap[ent(site)], lanebit);
-        const uint64_t nbh = lmap[ent(site)] | lmap[ent(s_up)] | lmap[ent(s_dn)] | lmap[ent(s_lf)] |
-                             lmap[ent(s_rt)];
-        if (lane < n) lmap[ent(site)] = 0;
+        uint64_t* const home = lmap + ent(site);
+        atomicOr((unsigned long long*)home, lane < n ? lanebit : 0ull);
+        const uint64_t e0 = *home, e1 = lmap[ent(s_up)], e2 = lmap[ent(s_dn)], e3 = lmap[ent(s_lf)], e4 = lmap[ent(s_rt)];
+        *home = 0;
+        const uint32_t off = MODEL == 0 ? 0u : (uint32_t)(((uint64_t)x.y * qm1) >> 32);
+        // bounds of the acceptance threshold less the lane's updates: with y = lb minus
+        // cur of the candidate bin, y > whi accepts and y < wlo rejects for certain
+        const Bound32 tb = bounds_of(x.z, x.w, band32);
+        const float whi = tb.hi - laneinc, wlo = tb.lo - laneinc;
+        const uint64_t nbh = e0 | e1 | e2 | e3 | e4;
         const uint64_t pm = nbh & (lanebit - 1);
         const uint64_t qm = nbh & ~(lanebit | (lanebit - 1));
         uint64_t* const fword = lrow + (WIDE ? rr * wpr + (cc >> 6) : rr);   // Ising: the flip's word
         const uint64_t fbit = 1ull << (cc & 63);
 
-        // 64 less the index of the first attempt that this one's flip makes out of date
-        // (0: there is none), in the upper half of the word that a step reads of its move
-        const int cut = (64 - (int)__builtin_popcountll((qm - 1) & ~qm)) << 16;
+        // the first attempt that this one's flip makes out of date (64: there is none), in
+        // the upper half of the word that a step reads of its move
+        const uint32_t cut = (uint32_t)__builtin_popcountll((qm - 1) & ~qm) << 16;
 
         // the chain: rounds from one evaluation of the lattice to the next
         uint32_t i = 0;                   // first attempt of the round
@@ -682,76 +693,86 @@ __device__ void sweep_wave(const Inst& I, const Tile& tile, char* smem)
                 const int nnew = (n0 == nv) + (n1 == nv) + (n2 == nv) + (n3 == nv);
                 d = nold - nnew;
             }
-            const int d4 = d << 2, word = cut + d4;
+            const uint32_t word = cut + ((uint32_t)d & 63u);
+            int addr = (idx + d) << 2;
+            float gp = bperm_f(cur, addr);
+            __builtin_amdgcn_sched_barrier(0);
             // zall: moves within the bin (d = 0, always accepted); stale: attempts with
-            // one of them in the neighbourhood; drop: how many attempts the first that is
-            // out of date, as far as the moves made go, cuts off the chunk's 64; open:
-            // the attempts before it with d != 0 that are not yet decided
+            // one of them in the neighbourhood; lim: the first attempt that is out of date,
+            // as far as the moves made go; after: the attempts behind the last move.  An
+            // attempt of no concern to the round has no threshold it could pass.
             const uint64_t run = live & (~0ull << i);
             const uint64_t zall = __builtin_amdgcn_ballot_w64(d == 0) & run;
             const uint64_t stale = __builtin_amdgcn_ballot_w64((pm & zall) != 0) & run;
             const uint64_t nz = run & ~zall;
-            uint64_t open = nz & (stale - 1) & ~stale;
-            int drop = 64 - (int)__builtin_popcountll((stale - 1) & ~stale);
+            const bool mine = __builtin_amdgcn_inverse_ballot_w64(nz);
+            const float wh = mine ? whi : __builtin_inff(), wl = mine ? wlo : __builtin_inff();
+            uint64_t after = ~0ull;
+            uint32_t lim = min(first_bit(stale), 64u);
             uint64_t moved = 0;           // accepted moves with d != 0 of the round
             for (;;) {
                 // Steps from one accepted move with d != 0 to the next.  A step is one
-                // dependent chain (look up, compare, first accepted, its bin change) whose
-                // instructions a wave alone on its SIMD issues one by one (4.5 cycles for
-                // most, 6 in FP64, 11 for v_readlane, 24 for a branch): so there is one
+                // dependent chain (look up, compare, first not certainly rejected, its bin
+                // change) whose instructions a wave alone on its SIMD issues one by one (4.5
+                // cycles for most, 11 for v_readlane, 24 for a branch): so there is one
                 // branch, the next step's lookup is issued before this one is known to be a
-                // move, and the bookkeeping runs while it is under way.
-                uint64_t gt, ge, next = bit_then(safe, idx, open);
-                uint32_t ja;
-                int to;
-                float jf, gn, gp = bperm_f(cur, d4 + (idx << 2));
+                // move, and the bookkeeping runs while it is under way.  at: the
+                // walker's bin, modulo 64, under the words' upper halves; addr: 4 (at + d).
+                uint64_t gt, ge;
+                uint32_t ja, at = (uint32_t)idx, w, lim1 = bit_then(safe, at, lim);
+                float jf, gn;
                 auto step = [&]() {
                     const float y = lb - gp;
-                    gt = __builtin_amdgcn_ballot_w64(y > whi);
-                    ge = __builtin_amdgcn_ballot_w64(y >= wlo);       // holds gt
-                    const uint64_t acc = gt & next;
-                    ja = first_bit(acc);
+                    ge = __builtin_amdgcn_ballot_w64(y >= wl);        // holds gt
+                    gt = __builtin_amdgcn_ballot_w64(y > wh);
+                    ja = first_bit(ge & after);
                     jf = (float)(int)ja;
-                    cnt += lane == idx ? jf - je : 0.0f;              // the old bin's visits
-                    cur = __builtin_fmaf(cnt, inc32, g0);
+                    w = (uint32_t)__builtin_amdgcn_readlane((int)word, (int)ja);
+                    cnt = __builtin_fmaf(jf, hot, cnt);               // the old bin's visits
                     gn = rlf(gp, (int)ja);                            // the new bin's entry
-                    to = (idx << 2) + __builtin_amdgcn_readlane(word, (int)ja);
-                    gp = bperm_f(cur, d4 + to);                       // lane: bits 2 to 7
+                    addr += (int)(w << 2);
+                    cur = __builtin_fmaf(cnt, inc32, g0);
+                    gp = bperm_f(cur, addr);                          // lane: bits 2 to 7
                     __builtin_amdgcn_sched_barrier(0);
-                    // no move, or some attempt between the bounds: left to the code below
-                    return equal_then(gt, ge, acc) != 0;
+                    // none, or one between the bounds, or in a bin outside `safe`: left to
+                    // the code below
+                    return ja < bit_then(gt, ja, lim1);
                 };
                 auto move = [&]() {
-                    idx = (to >> 2) & 63;
-                    je = jf;
+                    at += w;
+                    lim = min(lim, w >> 16);
+                    after = ~1ull << (ja & 63);
+                    hot = __builtin_amdgcn_inverse_ballot_w64(1ull << (at & 63)) ? 1.0f : 0.0f;
+                    cnt = __builtin_fmaf(-jf, hot, cnt);
                     lb = __builtin_fmaf(-jf, inc32, gn);
-                    drop = max(drop, to >> 16);
-                    open = nz & (~0ull >> drop) & (~1ull << ja);
                     set_bit(moved, ja);
                 };
                 bool go = step();
                 while (go) {
                     move();
-                    next = bit_then(safe, idx, open);
+                    lim1 = bit_then(safe, at, lim);
                     __builtin_amdgcn_sched_barrier(0);
                     go = step();
                 }
-                cnt -= lane == idx ? jf - je : 0.0f;                  // the step not taken
-                cur = __builtin_fmaf(cnt, inc32, g0);
-                // the usual end of a round: nothing accepted, nothing between the bounds
-                if (equal_then(gt, ge, bit_then(safe, idx, 1)) != 0) break;
-                if (!((safe >> idx) & 1)) {
+                // the step not taken (cur of the walker's own bin is of no use to any attempt)
+                cnt = __builtin_fmaf(-jf, hot, cnt);
+                idx = (int)(at & 63);
+                const uint32_t end = bit_pick(safe, at, lim, 65);
+                if (__builtin_expect(min(ja, 64u) >= end, 1)) break;  // the usual end of a round
+                if (end == 65) {
                     settle(64 - (int)__builtin_clzll(moved));         // up to the last move
+                    addr = (idx + d) << 2;
+                    gp = bperm_f(cur, addr);
                     continue;
                 }
                 // attempts between the bounds are decided exactly, in order, up to the
                 // first accepted one
+                const uint64_t open = nz & after & (~0ull >> (64 - lim));
                 uint64_t acc = gt & open, amb = ge & ~gt & open & (acc - 1) & ~acc;
-                if (__builtin_expect((acc | amb) == 0, 1)) break;
                 while (amb) {
                     const uint32_t kk = first_bit(amb);
                     const int cand = idx + __builtin_amdgcn_readlane(d, (int)kk);
-                    const double here = __builtin_fma((double)(rlf(cnt, idx) + ((float)kk - je)), incv, rld(gl, idx));
+                    const double here = __builtin_fma((double)(rlf(cnt, idx) + (float)kk), incv, rld(gl, idx));
                     const double there = __builtin_fma((double)rlf(cnt, cand), incv, rld(gl, cand));
                     if (wave_decide(I, T0 + (uint64_t)j0 + (uint64_t)kk, (uint32_t)slot, here - there, lane)) {
                         acc = 1ull << kk;
@@ -762,24 +783,27 @@ __device__ void sweep_wave(const Inst& I, const Tile& tile, char* smem)
                 if (!acc) break;
                 ja = first_bit(acc);
                 jf = (float)(int)ja;
-                cnt += lane == idx ? jf - je : 0.0f;
+                cnt = __builtin_fmaf(jf, hot, cnt);
                 cur = __builtin_fmaf(cnt, inc32, g0);
-                gn = rlf(cur, idx + __builtin_amdgcn_readlane(d, (int)ja));
-                to = (idx << 2) + __builtin_amdgcn_readlane(word, (int)ja);
+                w = (uint32_t)__builtin_amdgcn_readlane((int)word, (int)ja);
+                gn = rlf(cur, (int)((at + w) & 63));
                 move();
+                idx = (int)(at & 63);
+                addr = (idx + d) << 2;
+                gp = bperm_f(cur, addr);
             }
             // the round's flips: its accepted moves, and its d = 0 moves before the first
             // out-of-date attempt
-            const uint64_t flips = (zall & (~0ull >> drop)) | moved;
+            const uint64_t flips = (zall & (~0ull >> (64 - lim))) | moved;
             if (__builtin_amdgcn_inverse_ballot_w64(flips)) {
                 if (MODEL == 0) atomicXor((unsigned long long*)fword, fbit);
                 else llat[site] = (uint8_t)nv;
             }
-            i = 64 - drop;
+            i = lim;
             if (i >= (uint32_t)n) break;  // else evaluated again on the lattice as it stands now
         }
         settle(n);
-        je = lb = 0.0f;
+        cnt = lb = 0.0f;
     }
     store_window();
 
