@@ -18,6 +18,9 @@ HIPCC_FLAGS = [
     # FP expressions evaluate as written: the exact ln g arithmetic and the
     # double-double error-free transformations must not be fused implicitly
     "-ffp-contract=off",
+    # inner loops of a few dozen instructions: fetched from wherever they happen to begin,
+    # the wave sweep's step varies by 3 %; 32 and 64 cost more in padding than they give
+    "-falign-loops=16",
     # no packed-FP32 instructions anywhere in device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]

@@ -163,6 +163,9 @@ struct rewl_handle {
     int persist_grid = 0;       // its blocks: as many as the GPU holds at once
     Tile* d_wtiles = nullptr;
     int nwtiles = 0;
+    Tile* d_wtmp = nullptr;     // for their reordering by the work of the last interval:
+    uint32_t* d_wcost = nullptr; // of each block
+    int norder = 0;             // blocks to reorder (0: no more of them than CUs)
     int wave_threads = 64;
     size_t max_lds_wave = 0;
     int2* d_merge = nullptr;
@@ -258,14 +261,15 @@ rewl_status enqueue_interval(rewl_handle* H, bool time_it)
                            H->d_tiles, H->ntiles);
     if (H->nwtiles > 0)
         hipLaunchKernelGGL(k_sweep_wave, dim3(H->nwtiles), dim3(H->wave_threads), H->max_lds_wave,
-                           H->stream, H->d_insts, H->d_wtiles, H->nwtiles);
+                           H->stream, H->d_insts, H->d_wtiles, H->norder ? H->d_wcost : nullptr);
     if (time_it) HIP_TRY(hipEventRecord(H->ev[2], H->stream));
     hipLaunchKernelGGL(k_merge, dim3(H->nmerge), dim3(256), 0, H->stream, H->d_insts, H->d_merge);
     if (H->exch_threads > 0)
         hipLaunchKernelGGL(k_exchange, dim3((H->exch_threads + 3) / 4), dim3(256), 0, H->stream,
                            H->d_insts, H->d_exch_start, H->n);
-    hipLaunchKernelGGL(k_advance, dim3((H->n + 63) / 64), dim3(64), 0, H->stream, H->d_insts, H->n,
-                       H->d_queue);
+    const int nt = H->norder > 0 ? 256 : 64;
+    hipLaunchKernelGGL(k_advance, dim3((H->n + nt - 1) / nt), dim3(nt), 0, H->stream, H->d_insts, H->n, H->d_queue,
+                       H->d_wtiles, H->d_wtmp, H->d_wcost, H->norder);
     if (time_it) HIP_TRY(hipEventRecord(H->ev[3], H->stream));
     HIP_TRY(hipGetLastError());
     return REWL_OK;
@@ -823,8 +827,8 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
     }
     rewl_status s = H->alloc(&H->d_ctr, n);
     if (s != REWL_OK) return bail(s);
-    if ((s = H->alloc(&H->d_queue, 1)) != REWL_OK) return bail(s);
-    if (hipMemsetAsync(H->d_queue, 0, 4, H->stream) != hipSuccess)
+    if ((s = H->alloc(&H->d_queue, 2)) != REWL_OK) return bail(s);
+    if (hipMemsetAsync(H->d_queue, 0, 8, H->stream) != hipSuccess)
         return bail(fail(REWL_E_DEVICE, "memset failed"));
     if (hipHostMalloc((void**)&H->h_ctr, sizeof(InstCtr) * n, hipHostMallocDefault) != hipSuccess)
         return bail(fail(REWL_E_NOMEM, "hipHostMalloc failed"));
@@ -845,12 +849,17 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
     });
     H->ntiles = (int)tiles.size();
     H->nwtiles = (int)wtiles.size();
+    H->norder = H->nwtiles > n_cu ? H->nwtiles : 0;
     H->nmerge = (int)merges.size();
     H->exch_threads = exch_start.back();
     H->slot_threads = slot_start.back();
     if ((s = H->alloc(&H->d_insts, n)) != REWL_OK) return bail(s);
     if ((s = H->alloc(&H->d_tiles, tiles.size())) != REWL_OK) return bail(s);
     if ((s = H->alloc(&H->d_wtiles, wtiles.size())) != REWL_OK) return bail(s);
+    if ((s = H->alloc(&H->d_wtmp, H->norder)) != REWL_OK) return bail(s);
+    if ((s = H->alloc(&H->d_wcost, H->norder)) != REWL_OK) return bail(s);
+    if (hipMemsetAsync(H->d_wcost, 0, (size_t)std::max(H->norder, 1) * 4, H->stream) != hipSuccess)
+        return bail(fail(REWL_E_DEVICE, "memset failed"));
     if ((s = H->alloc(&H->d_merge, merges.size())) != REWL_OK) return bail(s);
     if ((s = H->alloc(&H->d_exch_start, exch_start.size())) != REWL_OK) return bail(s);
     if ((s = H->alloc(&H->d_slot_start, slot_start.size())) != REWL_OK) return bail(s);

@@ -495,10 +495,11 @@ __device__ __forceinline__ int ising_d_words(const uint64_t* rows, int wpr, int 
 // sets 600 (Ising L=64, middle windows: 26 steps and 2.2 rounds per chunk).  A step in
 // FP64 on exact values took 390 cycles, one of 34 instructions 270.  Interval of 10^4
 // attempts, us, with FP64 steps / 34 instructions / now: Ising L=32, 128 walkers 1090 / 695
-// / 545; L=64, 1024: 1100 / 656 / 512; L=128, 2048: 1249 / 811 / 690; Potts q=10 L=32, 4096
-// (4 to a SIMD): 1699 / 970 / 842; L=64, 4096: 1725 / 1180 / 984.
+// / 554; L=64, 1024: 1100 / 656 / 517; L=128, 2048: 1249 / 811 / 608; Potts q=10 L=32, 4096
+// (4 to a SIMD): 1699 / 970 / 633; L=64, 4096: 1725 / 1180 / 821 (the last three by the
+// order of the blocks too, order_tiles).
 template <int MODEL, bool WIDE, bool HG>
-__device__ void sweep_wave(const Inst& I, const Tile& tile, char* smem)
+__device__ void sweep_wave(const Inst& I, const Tile& tile, char* smem, uint32_t* __restrict__ cost)
 {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int G = tile.nw;
@@ -634,6 +635,7 @@ __device__ void sweep_wave(const Inst& I, const Tile& tile, char* smem)
         lb = -(float)j * inc32;
     };
     settle(0);
+    uint32_t work = 0;                    // of the interval, in steps
     const float rL = 1.0f / (float)L;
     const float band32 = (float)band + kErr32;
     const uint64_t lanebit = 1ull << lane;
@@ -799,6 +801,7 @@ __device__ void sweep_wave(const Inst& I, const Tile& tile, char* smem)
                 if (MODEL == 0) atomicXor((unsigned long long*)fword, fbit);
                 else llat[site] = (uint8_t)nv;
             }
+            work += (uint32_t)__builtin_popcountll(moved) + 4;           // a round costs about 4
             i = lim;
             if (i >= (uint32_t)n) break;  // else evaluated again on the lattice as it stands now
         }
@@ -806,6 +809,7 @@ __device__ void sweep_wave(const Inst& I, const Tile& tile, char* smem)
         cnt = lb = 0.0f;
     }
     store_window();
+    if (lane == 0 && cost) atomicMax(cost, work);
 
     // ---- write back (HG: the window's store above is the write back)
     if (!HG)
@@ -855,26 +859,27 @@ __device__ void sweep_wave(const Inst& I, const Tile& tile, char* smem)
 }
 
 __global__ void __launch_bounds__(512) k_sweep_wave(const Inst* __restrict__ insts,
-                                                    const Tile* __restrict__ tiles, int ntiles)
+                                                    const Tile* __restrict__ tiles, uint32_t* __restrict__ cost)
 {
     extern __shared__ __align__(16) char smem[];
     const Tile tile = tiles[blockIdx.x];
     const Inst& I = insts[tile.inst];
     if (I.ctr->all_done) return;
+    if (cost) cost += blockIdx.x;
     const bool wide = I.wpr > 1;
     if (I.hglobal) {
         if (I.model == 0) {
-            if (wide) sweep_wave<0, true, true>(I, tile, smem);
-            else sweep_wave<0, false, true>(I, tile, smem);
+            if (wide) sweep_wave<0, true, true>(I, tile, smem, cost);
+            else sweep_wave<0, false, true>(I, tile, smem, cost);
         } else {
-            sweep_wave<1, false, true>(I, tile, smem);
+            sweep_wave<1, false, true>(I, tile, smem, cost);
         }
     } else {
         if (I.model == 0) {
-            if (wide) sweep_wave<0, true, false>(I, tile, smem);
-            else sweep_wave<0, false, false>(I, tile, smem);
+            if (wide) sweep_wave<0, true, false>(I, tile, smem, cost);
+            else sweep_wave<0, false, false>(I, tile, smem, cost);
         } else {
-            sweep_wave<1, false, false>(I, tile, smem);
+            sweep_wave<1, false, false>(I, tile, smem, cost);
         }
     }
 }
@@ -1053,10 +1058,58 @@ __global__ void __launch_bounds__(256) k_exchange(const Inst* __restrict__ insts
 }
 
 // ----------------------------------------------------------------- advance
-__global__ void k_advance(const Inst* __restrict__ insts, int n_inst, int32_t* __restrict__ queue)
+// The wave sweep's blocks, those with most work first.  Windows differ by an order of
+// magnitude in the work of an interval (moves and rounds per attempt); blocks start in
+// their order, a SIMD serves its oldest wave first, and the launch ends with its slowest
+// wave.  By one block, in 64 classes of the most work that a wave of the block had since
+// the last time; which of a class comes first is left open.  us per interval of 10^4
+// attempts, in the windows' order and so: Potts q=10 L=32, 4096 walkers 842 and 633; L=64
+// 984 and 821; Ising L=128, 2048 walkers 690 and 608.  (Priorities instead, s_setprio by
+// window: 650, 984 and 655; order and priorities: no better.)
+constexpr int kOrderClasses = 64, kOrderEvery = 8;
+__device__ void order_tiles(Tile* tiles, Tile* tmp, uint32_t* cost, int ntiles)
+{
+    __shared__ uint32_t top, start[kOrderClasses];
+    const int tid = threadIdx.x;
+    if (tid == 0) top = 0;
+    if (tid < kOrderClasses) start[tid] = 0;
+    __syncthreads();
+    uint32_t mx = 0;
+    for (int i = tid; i < ntiles; i += blockDim.x) mx = cost[i] > mx ? cost[i] : mx;
+    atomicMax(&top, mx);
+    __syncthreads();
+    const uint64_t all = (uint64_t)top + 1;
+    auto class_of = [&](int i) { return kOrderClasses - 1 - (int)((uint64_t)cost[i] * kOrderClasses / all); };
+    for (int i = tid; i < ntiles; i += blockDim.x) atomicAdd(&start[class_of(i)], 1u);
+    __syncthreads();
+    if (tid == 0)
+        for (uint32_t c = 0, sum = 0; c < kOrderClasses; ++c) {
+            const uint32_t v = start[c];
+            start[c] = sum;
+            sum += v;
+        }
+    __syncthreads();
+    for (int i = tid; i < ntiles; i += blockDim.x) tmp[atomicAdd(&start[class_of(i)], 1u)] = tiles[i];
+    __syncthreads();
+    for (int i = tid; i < ntiles; i += blockDim.x) {
+        tiles[i] = tmp[i];
+        cost[i] = 0;
+    }
+}
+
+// queue[0]: the persistent sweep's tile queue; queue[1]: intervals so far.  ntiles: the wave
+// sweep's blocks if their order matters, else 0.
+__global__ void k_advance(const Inst* __restrict__ insts, int n_inst, int32_t* __restrict__ queue, Tile* tiles, Tile* tmp,
+                          uint32_t* cost, int ntiles)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == 0) *queue = 0;                 // the persistent sweep's tile queue
+    if (blockIdx.x == 0 && ntiles > 0) {
+        const int t = queue[1];
+        __syncthreads();
+        if (threadIdx.x == 0) queue[1] = (t + 1) & 0xffff;
+        if (t % kOrderEvery == 0) order_tiles(tiles, tmp, cost, ntiles);
+    }
+    if (i == 0) *queue = 0;
     if (i >= n_inst) return;
     InstCtr* c = insts[i].ctr;
     if (!c->stopped) {

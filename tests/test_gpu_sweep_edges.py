@@ -79,3 +79,18 @@ def test_auto_splits_a_batch(rw, small, lanes):
     for other in states[1:]:
         for a, b in zip(states[0], other):
             assert_same(a, b, f"{small} small instances")
+
+
+@pytest.mark.parametrize("use_graph", [0, 1])
+def test_blocks_in_order_of_work(rw, use_graph):
+    """More blocks than the GPU has CUs, of windows with unequal work: reordered on the device
+    between the intervals, every walker swept once in each of them."""
+    kw = dict(model="potts", q=10, L=8, n_windows=3, m=512, kfinal=12, X=130, seed=77)
+    gpu = rw.Rewl([rw.make_config(**kw)], tune=rw.make_tune("wave", walkers_per_block=2, use_graph=use_graph))
+    orc = O.Sim(O.make_config(**kw))
+    assert gpu.info()["walkers_per_block"] == 2                          # 768 blocks
+    for n in (1, 1, 8, 9):
+        gpu.run(n)
+        orc.run(n)
+        assert_same(gpu.state(), orc.state(), f"after {orc.t} intervals")
+    gpu.close()
