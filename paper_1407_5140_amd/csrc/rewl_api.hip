@@ -678,12 +678,13 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
     // limited by the walkers whose tables the LDS holds at once (about 0.03 + 0.075 us per
     // KB of a walker's tables), and an interval takes it 2.9 ms however few they are.  So
     // it takes the instances of small tables where there are enough of them.  Measured,
-    // ms per interval, lane against wave: Ising L=16, 131 072 walkers (0.7 KB) 9.0 / 25.9,
-    // 16 384 walkers 2.7 / 3.5; Potts q=10 L=16, 131 072 (1.2 KB) 12.9 / 22.0; Ising L=64,
-    // 32 768 (2.5 KB) 6.8 / 5.5; Potts q=10 L=32, 32 768 (2.8 KB) 8.1 / 4.8; 64 unequal
-    // instances, 65 280 walkers: all lane 11.2, all wave 11.4, by this rule 10.8.
-    // Its lane tiles are capped at 40 KB (Ising L=16, 131 072 walkers: 10.3 at 53 KB, 8.9)
-    // and handed out by the queue (11.5 to 10.2 there).
+    // ms per interval, lane against wave: Ising L=16 (0.7 KB), 131 072 walkers 8.8 / 22.5,
+    // 32 768 3.4 / 5.9, 16 384 2.6 / 3.1, 8192 2.1 / 1.7; Potts q=10 L=16 (1.2 KB), 131 072
+    // 12.1 / 19.0, 32 768 3.7 / 4.9, 16 384 3.0 / 2.6; Ising L=32, 65 536 7.2 / 9.2; Ising
+    // L=64, 32 768 (2.5 KB) 6.7 / 4.6; Potts q=10 L=32, 32 768 (2.8 KB) 8.3 / 4.0; 64 unequal
+    // instances, 65 280 walkers: all lane 11.3, all wave 9.5, by this rule 9.6.  Its lane tiles
+    // are capped at 40 KB (Ising L=16, 131 072 walkers: 10.3 at 53 KB, 8.8) and handed out by
+    // the queue (11.5 to 10.2 there).
     constexpr size_t kLaneBytes = 1792, kLaneTile = size_t(40) << 10;
     constexpr int64_t kLaneWalkers = 16384;
     int64_t total_walkers = 0, small_walkers = 0;

@@ -3,11 +3,12 @@
 // One interval of replica-exchange Wang-Landau (arXiv:1407.5140 Sec. II.A):
 //   k_sweep    X single-site attempts per walker, one walker per lane, the
 //              walker's lattice and histogram and its window's ln g base in LDS,
-//              drawn by a second wave; flatness test of every walker in the epilogue
+//              drawn by a second wave (k_sweep_persist: the same from a queue of tiles;
+//              k_sweep_wave: one walker per wave); flatness test in the epilogue
 //   k_merge    per window: when all m walkers are flat, average ln g, reset H,
 //              halve ln f, detect convergence
 //   k_exchange Eq. (1) between neighbouring windows, alternating pairings
-//   k_advance  interval counter and termination bookkeeping
+//   k_advance  interval counter, termination bookkeeping, order of the sweep's blocks
 // All interval state lives in device memory, so an interval is a fixed
 // sequence of launches that can be captured once and replayed.
 #include "rewl_device.hpp"
@@ -21,9 +22,9 @@ namespace rewl {
 //   lat  Ising [L*wpr << lnw] u64 words / Potts [N << lnw] bytes
 //   draws [2][8 (Ising) or 4 (Potts) << lnw]: the next attempts of every walker, twice
 // A block is two waves: wave 0 walks, wave 1 draws the next attempts of its walkers
-// meanwhile, down to the sites whose spins an attempt reads.  (Drawn by the whole GPU in a launch of its own, through a buffer
-// of 12 bytes per attempt in memory, the 65 280-walker batch took 3.9 + 13.1 ms per
-// interval, now 11.3.)
+// meanwhile, down to the sites whose spins an attempt reads.  (Drawn by the whole GPU in
+// a launch of its own, through a buffer of 12 bytes per attempt in memory, the
+// 65 280-walker batch took 3.9 + 13.1 ms per interval, now 11.3.)
 // A move changes the bin by at most 2 (Ising) or 4 (Potts), so a proposal
 // outside the window lands in a pad, sees ln g = +inf and is rejected.
 constexpr int kPad = 4;
