@@ -1108,7 +1108,10 @@ __global__ void k_advance(const Inst* __restrict__ insts, int n_inst, int32_t* _
         const int t = queue[1];
         __syncthreads();
         if (threadIdx.x == 0) queue[1] = (t + 1) & 0xffff;
-        if (t % kOrderEvery == 0) order_tiles(tiles, tmp, cost, ntiles);
+        // the time it takes grows with the blocks: so does the time between (every 8th interval
+        // of 10^2 attempts, 65 536 blocks 1545 us per interval, so 1506, never 1494; of 10^3,
+        // 16 384 blocks 973, 964 and 1004)
+        if (t % (kOrderEvery + (ntiles >> 7)) == 0) order_tiles(tiles, tmp, cost, ntiles);
     }
     if (i == 0) *queue = 0;
     if (i >= n_inst) return;
