@@ -445,7 +445,7 @@ std::vector<Span> spans_of(rewl_handle* H, int i)
     v.push_back({d.rid, S * 4});
     v.push_back({d.rt_state, S});
     v.push_back({d.rt_count, S * 4});
-    v.push_back({d.ctr, sizeof(InstCtr)});
+    v.push_back({d.ctr, kCtrBytes});
     return v;
 }
 }  // namespace
@@ -1082,7 +1082,7 @@ rewl_status rewl_get_state(rewl_handle* H, int32_t i, uint8_t* spins, int32_t* b
     std::vector<double> base;
     std::vector<uint64_t> lat;
     InstCtr ctr;
-    std::vector<Piece> q = {{kk.data(), d.k, h * 4}, {dd.data(), d.done, h * 4}, {&ctr, d.ctr, sizeof(ctr)}};
+    std::vector<Piece> q = {{kk.data(), d.k, h * 4}, {dd.data(), d.done, h * 4}, {&ctr, d.ctr, sizeof(InstCtr)}};
     if (lng && !Hout) {
         Hd.resize(S * WB);
         Hout = Hd.data();
@@ -1133,7 +1133,7 @@ rewl_status rewl_get_stats(rewl_handle* H, int32_t i, rewl_stats* out, int64_t* 
     std::vector<int32_t> kk(hi.h), rt(hi.S);
     InstCtr c;
     std::vector<Piece> q = {{kk.data(), hi.dev.k, (size_t)hi.h * 4}, {rt.data(), hi.dev.rt_count, (size_t)hi.S * 4},
-                            {&c, hi.dev.ctr, sizeof(c)}};
+                            {&c, hi.dev.ctr, sizeof(InstCtr)}};
     if (ex_prop) q.push_back({ex_prop, hi.dev.ex_prop, (size_t)hi.h * 8});
     if (ex_acc) q.push_back({ex_acc, hi.dev.ex_acc, (size_t)hi.h * 8});
     if ((s = fetch(H, q)) != REWL_OK) return s;

@@ -8,6 +8,7 @@
 // * Per-instance descriptors shared by the kernels.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace rewl {
@@ -197,8 +198,9 @@ __device__ __forceinline__ float lower_of(float hi, float e) { return __builtin_
 // ---------------------------------------------------------- descriptors
 enum : int32_t { kErrOverflow = 1, kErrInitStuck = 2, kErrExactness = 4 };
 
-// Device counters of one instance (one cache line each would be overkill).
-struct InstCtr {
+// Device counters of one instance.  A checkpoint holds the first kCtrBytes; in the array
+// of a batch every instance's begin at a multiple of 16 bytes, as k_collect reads them.
+struct alignas(16) InstCtr {
     int64_t t;          // completed intervals
     int64_t slow;       // acceptance decisions taken by the exact slow path
     int32_t all_done;   // every window converged
@@ -208,6 +210,8 @@ struct InstCtr {
     int32_t queue;      // sweep tile queue head
     int32_t pad;
 };
+constexpr size_t kCtrBytes = 40;
+static_assert(offsetof(InstCtr, pad) + sizeof(int32_t) == kCtrBytes && sizeof(InstCtr) % 16 == 0, "layout of the counters");
 
 struct Inst {
     // problem
