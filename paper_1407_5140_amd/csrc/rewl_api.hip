@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "../../include/rewl.h"
+#include "host_copy.hpp"
 #include "rewl_kernels.hip"
 #include "ensemble_kernels.hip"
 
@@ -177,7 +178,7 @@ struct rewl_handle {
     size_t max_lds = 0;
     InstCtr* d_ctr = nullptr;
     InstCtr* h_ctr = nullptr;   // pinned
-    char* h_stage = nullptr;    // pinned, kStageBytes: small pieces of state on their way to the host
+    char* h_stage = nullptr;    // pinned, kStageBytes: small pieces of state on their way to the host (may be null)
     bool started = false;
     rewl_tune tune{};
     hipGraphExec_t gexec = nullptr;
@@ -304,92 +305,10 @@ rewl_status step(rewl_handle* H)
     return REWL_OK;
 }
 
-// ---- state on its way to the host.  A copy into pageable memory costs 10 to 15 us
-// whatever its size, and a state has 9 to 15 pieces per instance: pieces up to
-// kPieceBytes are therefore written into the handle's pinned stage by k_collect, up
-// to kCollect of them per launch, and copied out after one wait (4-walker Ising L = 8
-// instance: state 156 -> 32 us, checkpoint 217 -> 15 us).
-constexpr size_t kStageBytes = size_t(1) << 20, kPieceBytes = size_t(1) << 16;
-
-// Large copies into pageable memory go through two pinned slots in turn, the host
-// copying one out while the other fills (50 MB: 2.9 -> 2.3 ms).
-constexpr size_t kSlotBytes = size_t(4) << 20;
-hipError_t copy_out(hipStream_t st, void* dst, const void* src, size_t bytes)
-{
-    if (bytes < 2 * kSlotBytes) return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, st);
-    struct Slots {
-        char* p = nullptr;
-        hipEvent_t done[2] = {nullptr, nullptr};
-        ~Slots()
-        {
-            for (hipEvent_t e : done)
-                if (e) (void)hipEventDestroy(e);
-            if (p) (void)hipHostFree(p);
-        }
-    } s;
-    hipError_t e = hipHostMalloc((void**)&s.p, 2 * kSlotBytes, hipHostMallocDefault);
-    for (int i = 0; i < 2 && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&s.done[i], hipEventDisableTiming);
-    const size_t n = (bytes + kSlotBytes - 1) / kSlotBytes;
-    auto size_of = [&](size_t k) { return std::min(kSlotBytes, bytes - k * kSlotBytes); };
-    for (size_t k = 0; k <= n && e == hipSuccess; ++k) {
-        if (k < n) {
-            e = hipMemcpyAsync(s.p + (k & 1) * kSlotBytes, (const char*)src + k * kSlotBytes, size_of(k), hipMemcpyDeviceToHost, st);
-            if (e == hipSuccess) e = hipEventRecord(s.done[k & 1], st);
-        }
-        if (k > 0 && e == hipSuccess && (e = hipEventSynchronize(s.done[(k - 1) & 1])) == hipSuccess)
-            std::memcpy((char*)dst + (k - 1) * kSlotBytes, s.p + ((k - 1) & 1) * kSlotBytes, size_of(k - 1));
-    }
-    if (e != hipSuccess) (void)hipStreamSynchronize(st);      // nothing may still write the slots
-    return e;
-}
-
-struct Piece {
-    void* dst;
-    const void* src;
-    size_t bytes;
-};
-
 rewl_status fetch(rewl_handle* H, const std::vector<Piece>& pieces)
 {
-    size_t i = 0;
-    while (i < pieces.size()) {
-        Collect c{};
-        std::vector<const Piece*> staged;
-        size_t used = 0;
-        hipError_t e = hipSuccess;
-        auto collect = [&]() {
-            void* args[] = {&c, &H->h_stage};
-            const hipError_t r = hipLaunchKernel((const void*)k_collect, dim3(c.n), dim3(256), args, 0, H->stream);
-            c.n = 0;
-            return r;
-        };
-        for (; i < pieces.size(); ++i) {               // one stage full
-            const Piece& q = pieces[i];
-            if (q.bytes == 0) continue;
-            if (q.bytes > kPieceBytes) {
-                e = copy_out(H->stream, q.dst, q.src, q.bytes);
-                if (e != hipSuccess) break;
-                continue;
-            }
-            const size_t room = (q.bytes + 15) & ~size_t(15);
-            if (used + room > kStageBytes) break;
-            c.src[c.n] = (const char*)q.src;
-            c.off[c.n] = (uint32_t)used;
-            c.bytes[c.n] = (uint32_t)q.bytes;
-            staged.push_back(&q);
-            used += room;
-            if (++c.n == kCollect && (e = collect()) != hipSuccess) break;
-        }
-        if (e == hipSuccess && c.n > 0) e = collect();
-        const hipError_t e2 = hipStreamSynchronize(H->stream);
-        if (e == hipSuccess) e = e2;
-        if (e != hipSuccess) return fail(REWL_E_DEVICE, std::string("copy to the host: ") + hipGetErrorString(e));
-        size_t off = 0;
-        for (const Piece* q : staged) {
-            std::memcpy(q->dst, H->h_stage + off, q->bytes);
-            off += (q->bytes + 15) & ~size_t(15);
-        }
-    }
+    const hipError_t e = copy_pieces(H->stream, H->h_stage, (const void*)k_collect, pieces);
+    if (e != hipSuccess) return fail(REWL_E_DEVICE, std::string("copy to the host: ") + hipGetErrorString(e));
     return REWL_OK;
 }
 
@@ -833,8 +752,10 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
         return bail(fail(REWL_E_DEVICE, "memset failed"));
     if (hipHostMalloc((void**)&H->h_ctr, sizeof(InstCtr) * n, hipHostMallocDefault) != hipSuccess)
         return bail(fail(REWL_E_NOMEM, "hipHostMalloc failed"));
-    if (hipHostMalloc((void**)&H->h_stage, kStageBytes, hipHostMallocDefault) != hipSuccess)
-        return bail(fail(REWL_E_NOMEM, "hipHostMalloc failed"));
+    if (hipHostMalloc((void**)&H->h_stage, kStageBytes, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();                             // the pieces are copied one by one then
+        H->h_stage = nullptr;
+    }
     if (hipMemsetAsync(H->d_ctr, 0, sizeof(InstCtr) * n, H->stream) != hipSuccess)
         return bail(fail(REWL_E_DEVICE, "memset failed"));
     for (int i = 0; i < n; ++i) {

@@ -11,6 +11,7 @@
 //   k_advance  interval counter, termination bookkeeping, order of the sweep's blocks
 // All interval state lives in device memory, so an interval is a fixed
 // sequence of launches that can be captured once and replayed.
+#include "host_copy.hpp"
 #include "rewl_device.hpp"
 
 namespace rewl {
@@ -1380,13 +1381,7 @@ __global__ void __launch_bounds__(kConcatThreads) k_concat(const Inst* __restric
 }
 
 // ---------------------------------------------------------------- collect
-// Up to kCollect pieces of device memory (16-byte aligned) into one buffer, a block each.
-constexpr int kCollect = 64;
-struct Collect {
-    const char* src[kCollect];
-    uint32_t off[kCollect], bytes[kCollect];   // off: a multiple of 16
-    int32_t n;
-};
+// Up to kCollect pieces of device memory into one buffer, a block each (host_copy.hpp).
 __global__ void __launch_bounds__(256) k_collect(const Collect c, char* __restrict__ out)
 {
     const int p = blockIdx.x;
