@@ -333,7 +333,8 @@ def rewl_checkpoint(h) -> bytes:
 
 
 def rewl_restore(h, blob: bytes) -> None:
-    blob = bytes(blob)
+    if not isinstance(blob, bytes):
+        raise TypeError(f"a checkpoint is bytes, not {type(blob).__name__}")
     _check(_lib.rewl_restore(h, ctypes.cast(ctypes.c_char_p(blob), _vp), len(blob)), "rewl_restore")
 
 

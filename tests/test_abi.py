@@ -164,3 +164,10 @@ def test_tilt_density_model(rw):
     assert w[0] < w[-1] and lo[0] == 0 and hi[-1] == 2 * N
     with pytest.raises(rw.RewlError):
         rw.rewl_tilt_density(rw.make_config(model="ising", L=16, n_windows=0))
+
+
+@pytest.mark.parametrize("blob", [16, bytearray(16), [0] * 16, memoryview(bytes(16)), np.zeros(2), "0" * 16, None])
+def test_restore_takes_bytes_alone(rw, blob):
+    # whatever else bytes() would make something of is refused before the library sees it
+    with pytest.raises(TypeError):
+        rw.rewl_restore(None, blob)
