@@ -142,6 +142,7 @@ struct HostInst {
     rewl_config cfg;
     int N, W, h, m, S, WB, log2m, wpr, wpb, kind, placement, mapn;
     size_t lds;
+    bool far_draws = false;
     std::vector<int32_t> lo, hi, nreach;
     std::vector<uint8_t> mask;
     Inst dev;
@@ -660,6 +661,10 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
             while (wpb > 1 && sweep_lds_bytes(c.model, c.L, hi.wpr, hi.WB, wpb) > cap) wpb /= 2;
             hi.wpb = wpb;
             hi.lds = sweep_lds_bytes(c.model, c.L, hi.wpr, hi.WB, wpb);
+            if (hi.lds > (size_t)lds_limit) {                // one walker: its draws in device memory
+                hi.far_draws = true;
+                hi.lds = sweep_lds_bytes(c.model, c.L, hi.wpr, hi.WB, wpb, true);
+            }
             H->max_lds = std::max(H->max_lds, hi.lds);
         } else {
             WavePlan best;
@@ -701,6 +706,7 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
         if (s == REWL_OK) s = H->alloc(&d.done, h);
         if (s == REWL_OK) s = H->alloc(&d.flat, S);
         if (s == REWL_OK) s = H->alloc(&d.swaps, S);
+        if (s == REWL_OK && hi.far_draws) s = H->alloc(&d.draws, S * 2 * kDrawBytes);
         if (s == REWL_OK) s = H->alloc(&d.ex_prop, h);
         if (s == REWL_OK) s = H->alloc(&d.ex_acc, h);
         if (s == REWL_OK) s = H->alloc(&d.merges, h);

@@ -21,7 +21,8 @@ namespace rewl {
 //   base [kPad + WB + kPad]         window ln g base, +inf in the pads
 //   H    [(kPad + WB + kPad) << lnw] per-walker counts, bin-major (lane minor)
 //   lat  Ising [L*wpr << lnw] u64 words / Potts [N << lnw] bytes
-//   draws [2][8 (Ising) or 4 (Potts) << lnw]: the next attempts of every walker, twice
+//   draws [2][8 (Ising) or 4 (Potts) << lnw]: the next attempts of every walker, twice (in
+//                                    device memory where one walker's tables leave no room)
 // A block is two waves: wave 0 walks, wave 1 draws the next attempts of its walkers
 // meanwhile, down to the sites whose spins an attempt reads.  (Drawn by the whole GPU in
 // a launch of its own, through a buffer of 12 bytes per attempt in memory, the
@@ -31,12 +32,11 @@ namespace rewl {
 constexpr int kPad = 4;
 constexpr int kDrawBytes = 64;      // of one walker: 8 draws of 8 bytes or 4 of 16
 
-__host__ __device__ inline size_t sweep_lds_bytes(int model, int L, int wpr, int WB, int nw)
+__host__ __device__ inline size_t sweep_lds_bytes(int model, int L, int wpr, int WB, int nw, bool far_draws = false)
 {
-    const size_t nb = (size_t)WB + 2 * kPad;
-    size_t s = (nb * 8 + nb * nw * 4 + 15) & ~size_t(15);
-    s += ((model == 0 ? (size_t)L * wpr * 8 : (size_t)L * L) * nw + 15) & ~size_t(15);
-    return s + (size_t)2 * kDrawBytes * nw;
+    const size_t nb = (size_t)WB + 2 * kPad, al = far_draws ? 7 : 15;
+    const size_t s = (nb * 8 + nb * nw * 4 + al) & ~al, lat = (model == 0 ? (size_t)L * wpr * 8 : (size_t)L * L) * nw;
+    return far_draws ? s + lat : s + ((lat + al) & ~al) + (size_t)2 * kDrawBytes * nw;
 }
 
 // How many bytes of the word x differ from the byte v.
@@ -74,7 +74,7 @@ __device__ __forceinline__ double rld(double v, int l)
     return __builtin_bit_cast(double, rl64(__builtin_bit_cast(uint64_t, v), l));
 }
 
-template <int MODEL, int WPR>
+template <int MODEL, int WPR, bool FAR>
 __device__ void sweep_tile(const Inst& I, const Tile& tile, char* smem)
 {
     const int a = tile.window, nw = tile.nw, tid = threadIdx.x, lane = tid & 63;
@@ -85,13 +85,16 @@ __device__ void sweep_tile(const Inst& I, const Tile& tile, char* smem)
     const int nbins = WB + 2 * kPad;
     double* lbase = (double*)smem;                               // index kPad + bin
     uint32_t* lH = (uint32_t*)(lbase + nbins);                   // index (kPad + bin) << lnw | lane
-    char* latp = smem + ((nbins * 8 + (size_t)nbins * nw * 4 + 15) & ~size_t(15));
+    constexpr size_t kAlign = FAR ? 7 : 15;
+    char* latp = smem + ((nbins * 8 + (size_t)nbins * nw * 4 + kAlign) & ~kAlign);
     // Ising: .x row | col<<8 | row_up<<16 | row_down<<24 (periodic rows);
     // Potts: .x site | off<<16, off = floor(x1 (q-1) / 2^32), .y and .z the neighbours' sites;
     // last word: the bound of the threshold (upper_of)
     typedef uint32_t Draw __attribute__((ext_vector_type(MODEL ? 4 : 2)));
     constexpr int kDraws = kDrawBytes / (int)sizeof(Draw);
-    Draw* ring = (Draw*)(latp + (((MODEL == 0 ? (size_t)L * WPR * 8 : (size_t)N) * nw + 15) & ~size_t(15)));
+    Draw* ring;
+    if constexpr (FAR) ring = (Draw*)(I.draws + (size_t)slot0 * 2 * kDrawBytes);
+    else ring = (Draw*)(latp + (((MODEL == 0 ? (size_t)L * WPR * 8 : (size_t)N) * nw + 15) & ~size_t(15)));
     const int nthr = blockDim.x;
     const int lnw = __builtin_ctz(nw);                           // nw is a power of two
 
@@ -340,11 +343,15 @@ __device__ __forceinline__ void sweep_one_tile(const Inst* __restrict__ insts, c
 {
     const Inst& I = insts[tile.inst];
     if (I.ctr->all_done) return;
-    if (I.model == 0) {
-        if (I.wpr == 1) sweep_tile<0, 1>(I, tile, smem);
-        else sweep_tile<0, 2>(I, tile, smem);
+    if (__builtin_expect(I.draws != nullptr, 0)) {
+        // (Ising rows of one word have at most 4097 levels, 48 KB of tables)
+        if (I.model == 0) sweep_tile<0, 2, true>(I, tile, smem);
+        else sweep_tile<1, 1, true>(I, tile, smem);
+    } else if (I.model == 0) {
+        if (I.wpr == 1) sweep_tile<0, 1, false>(I, tile, smem);
+        else sweep_tile<0, 2, false>(I, tile, smem);
     } else {
-        sweep_tile<1, 1>(I, tile, smem);
+        sweep_tile<1, 1, false>(I, tile, smem);
     }
 }
 

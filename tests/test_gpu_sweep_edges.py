@@ -94,3 +94,24 @@ def test_blocks_in_order_of_work(rw, use_graph):
         orc.run(n)
         assert_same(gpu.state(), orc.state(), f"after {orc.t} intervals")
     gpu.close()
+
+
+@pytest.mark.parametrize("kind", ["lane", "lane-persist"])
+@pytest.mark.parametrize("short", [0, 16, 64, 128, 160])
+@pytest.mark.parametrize("kw", [dict(model="ising", L=128), dict(model="potts", q=10, L=100)],
+                         ids=lambda kw: f"{kw['model']}-L{kw['L']}")
+def test_lane_tables_that_fill_the_lds(rw, kind, short, kw):
+    """One walker's table, counts and lattice take the 160 KiB of a block up to `short` bytes
+    (and up to the queue's 16 bytes): its draws, 128 bytes, find room there or elsewhere."""
+    L, N = kw["L"], kw["L"] ** 2
+    W = N + 1 if kw["model"] == "ising" else 2 * N + 1
+    lattice = L * ((L + 63) // 64) * 8 if kw["model"] == "ising" else N
+    WB = min(W - 40, (163840 - 16 - short - lattice) // 12 - 8)
+    kw = dict(kw, n_windows=2, m=2, kfinal=12, X=300, seed=611, windows=([0, WB - 30], [WB - 1, W - 1]))
+    t = _tune(rw, kind)
+    t.walkers_per_block = 1
+    gpu = rw.Rewl([rw.make_config(**kw)], tune=t)
+    info = gpu.info()
+    gpu.close()
+    assert info["sweep_kind"] == "lane" and info["walkers_per_block"] == 1 and info["lds_bytes"] <= 163840
+    lockstep(rw, kw, t, (1, 2))
