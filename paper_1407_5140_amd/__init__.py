@@ -323,12 +323,32 @@ _new_bytes.argtypes = [ctypes.c_char_p, ctypes.c_ssize_t]
 _new_bytes.restype = ctypes.py_object
 
 
+_madvise = ctypes.CDLL(None).madvise
+_madvise.argtypes = [ctypes.c_size_t, ctypes.c_size_t, ctypes.c_int]
+_HUGEPAGE, _POPULATE_WRITE = 14, 23                          # Linux
+
+
+def _about_to_be_written(address: int, n: int) -> None:
+    """Memory of this module's own that the library is about to fill: faulted in page by page
+    under the copy, 48 MB take 11.7 ms, otherwise 4.5.  From 32 MiB on the C library gives a
+    block a mapping of its own, so the request for large pages goes with the block.  Smaller
+    blocks may lie among others: they are only faulted in ahead, which leaves no mark (48 MB
+    would take 6.3 ms that way; the first 12 MB 8 ms without it).  Both are hints."""
+    if n < 4 << 20:
+        return
+    page, advice = (2 << 20, _HUGEPAGE) if n >= 32 << 20 else (4096, _POPULATE_WRITE)
+    lo, hi = -(-address // page) * page, (address + n) // page * page
+    _madvise(lo, hi - lo, advice)
+
+
 def rewl_checkpoint(h) -> bytes:
     n = ctypes.c_size_t(0)
     _check(_lib.rewl_checkpoint(h, None, ctypes.byref(n)), "rewl_checkpoint")
     # the library writes into the bytes object itself: no cleared buffer, no second copy
     blob = _new_bytes(None, n.value)
-    _check(_lib.rewl_checkpoint(h, ctypes.cast(ctypes.c_char_p(blob), _vp), ctypes.byref(n)), "rewl_checkpoint")
+    at = ctypes.cast(ctypes.c_char_p(blob), _vp)
+    _about_to_be_written(at.value, n.value)
+    _check(_lib.rewl_checkpoint(h, at, ctypes.byref(n)), "rewl_checkpoint")
     return blob
 
 

@@ -1,7 +1,6 @@
 // rewl_api.hip -- host side of librewl: validation, layout, device state,
 // the interval launch sequence (plain or as a replayed HIP graph) and the C ABI.
 #include <hip/hip_runtime.h>
-#include <sys/mman.h>
 
 #include <algorithm>
 #include <cmath>
@@ -1309,10 +1308,6 @@ rewl_status rewl_checkpoint(rewl_handle* H, void* buf, size_t* len)
     std::memcpy(p, &magic, 8);
     std::memcpy(p + 8, &count, 8);
     p += 16;
-    // fresh memory of the caller's: large pages, so that writing it is not paced by page
-    // faults (a hint, for the pages that lie inside the buffer alone)
-    const uintptr_t big = size_t(2) << 20, lo = ((uintptr_t)p + big - 1) & ~(big - 1), hi = ((uintptr_t)buf + total) & ~(big - 1);
-    if (hi > lo) (void)madvise((void*)lo, hi - lo, MADV_HUGEPAGE);
     std::vector<Piece> q;
     for (int i = 0; i < H->n; ++i)
         for (const Span& sp : spans_of(H, i)) {
