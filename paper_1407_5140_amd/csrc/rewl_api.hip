@@ -1266,7 +1266,9 @@ rewl_status rewl_thermo(int32_t model, int32_t L, const double* lng, int32_t S, 
         // the device idle (calls with 20 001 levels: 16 x 600 level by level 0.43 ms, by the
         // contraction 0.58; 64 x 600: 1.27 and 0.84; with 1025 levels 121 and 117 us, 202
         // and 168).
-        const bool direct = (int64_t)S * nT < 10000;
+        // Its 32 threads to a temperature are 2^32 at 2^27 of them, more than a launch can have
+        // (the grid wraps around without an error); the other kernel has 8.
+        const bool direct = (int64_t)S * nT < 10000 || nT > (1 << 26);
         if (!direct) HIP_TRY(d_redo.alloc((size_t)S * nt8));
         HIP_TRY(hipMemcpy(d_lng.p, lng, in_b, hipMemcpyHostToDevice));
         HIP_TRY(hipMemcpy(d_T.p, T, (size_t)nT * 8, hipMemcpyHostToDevice));

@@ -247,3 +247,15 @@ def test_ensemble_reports_an_overlap_without_a_join(rw):
     with pytest.raises(rw.RewlError, match="no valid join"):
         gpu.concat(1)
     gpu.close()
+
+
+def test_thermo_takes_2_to_the_27_temperatures(rw):
+    """32 threads to a temperature would be more than a launch can have; u alone, 1 GiB."""
+    import ctypes
+    lg, n = np.log(np.array([2.0, 1.0, 12.0, 1.0, 2.0])), (1 << 27) + 9
+    T, u = np.full(n, 2.5), np.empty(n)
+    T[-9:] = np.linspace(1.0, 3.0, 9)
+    ref = rw.rewl_thermo("ising", 2, lg, T[-10:])[0][0]
+    p = lambda a: a.ctypes.data_as(ctypes.c_void_p)  # noqa: E731
+    assert rw._lib.rewl_thermo(0, 2, p(lg), 1, p(T), n, p(u), None, None) == rw.REWL_OK
+    assert np.allclose(u[-10:], ref, rtol=1e-12, atol=0) and np.allclose(u[: n - 9: 1 << 20], ref[0], rtol=1e-12, atol=0)
