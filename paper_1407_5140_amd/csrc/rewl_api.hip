@@ -1262,13 +1262,14 @@ rewl_status rewl_thermo(int32_t model, int32_t L, const double* lng, int32_t S, 
         if (c) HIP_TRY(d_c.alloc(out_b));
         if (f) HIP_TRY(d_f.alloc(out_b));
         const int nt8 = (nT + kThermoT - 1) / kThermoT;
-        // The contraction from 10 000 rows x temperatures on; below, its tiles leave most of
-        // the device idle (calls with 20 001 levels: 16 x 600 level by level 0.43 ms, by the
-        // contraction 0.58; 64 x 600: 1.27 and 0.84; with 1025 levels 121 and 117 us, 202
-        // and 168).
+        // The contraction from 8 rows and 16 000 rows x temperatures on: a tile has 16 rows,
+        // and its tiles leave most of the device idle below (calls level by level and by the
+        // contraction, us, at 1.9 <= T <= 2.1: 1 x 20 000, 20 001 levels 540 and 1900; 4 x 5000,
+        // 4097 levels 200 and 220; 8 x 2500, 16 385 levels 513 and 413; 64 x 312, 1025 levels
+        // 163 and 136; 64 x 156 139 and 125, but 152 and 160 at 0.05 <= T <= 0.2).
         // Its 32 threads to a temperature are 2^32 at 2^27 of them, more than a launch can have
         // (the grid wraps around without an error); the other kernel has 8.
-        const bool direct = (int64_t)S * nT < 10000 || nT > (1 << 26);
+        const bool direct = S < 8 || (int64_t)S * nT < 16000 || nT > (1 << 26);
         if (!direct) HIP_TRY(d_redo.alloc((size_t)S * nt8));
         HIP_TRY(hipMemcpy(d_lng.p, lng, in_b, hipMemcpyHostToDevice));
         HIP_TRY(hipMemcpy(d_T.p, T, (size_t)nT * 8, hipMemcpyHostToDevice));

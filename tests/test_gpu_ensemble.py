@@ -249,6 +249,24 @@ def test_ensemble_reports_an_overlap_without_a_join(rw):
     gpu.close()
 
 
+@pytest.mark.parametrize("rows,temps", [(8, 2000), (8, 1999), (7, 2287), (9, 1801), (17, 941), (33, 489), (16000, 1), (2003, 8)])
+@pytest.mark.parametrize("model,L", [("ising", 4), ("potts", 7), ("ising", 33)])
+def test_thermo_tiles_of_few_rows(rw, model, L, rows, temps):
+    """As test_thermo_tiles, on both sides of 8 rows and of 16 000 rows x temperatures; low
+    temperatures too, where one level has nearly all the weight."""
+    W = L * L + 1 if model == "ising" else 2 * L * L + 1
+    rng = np.random.default_rng(rows + temps)
+    x = np.linspace(-1, 1, W)
+    lg = L * L * 0.69 * (1 - x ** 2) + rng.normal(0, 0.3, (rows, W))
+    lg[:, rng.random(W) < 0.1] = -np.inf
+    lg[-1, :-1] = -np.inf
+    lg[-1, -1] = 1.0
+    some = sorted({0, rows // 2, rows - 2, rows - 1})
+    for T in (np.linspace(1.9, 2.1, temps), np.geomspace(0.1, 50.0, temps), np.linspace(0.4, 0.44, temps)):
+        g = rw.rewl_thermo(model, L, lg, T)
+        _assert_thermo(tuple(np.asarray(x)[some] for x in g), _oracle_thermo(model, L, [lg[i] for i in some], T))
+
+
 def test_thermo_takes_2_to_the_27_temperatures(rw):
     """32 threads to a temperature would be more than a launch can have; u alone, 1 GiB."""
     import ctypes
