@@ -47,12 +47,15 @@ __global__ void __launch_bounds__(256) k_boot_mean(const double* const* __restri
 // G = e^{ln g - ln g(Ek') - b (E - Ek)} scaled to at most 1, K = e^{-(1/T - b)(E - Ek)}
 // with b in the middle of the tile's 1/T: so one exponential per row and level and a
 // table of 64 per temperature (the same for every block) take the place of one per
-// row, level and temperature, and sums of w, w (E - Ek) and w (E - Ek)^2 for 16 rows
-// x 16 temperatures are FP64 matrix instructions.  A block's sums join the running
-// ones under their scale, kept to twice the double precision, about the Ek of the
-// largest block so far (so the variance loses little).  One block per tile, its 8
+// row, level and temperature, and sums of w, w (E - Er) and w (E - Er)^2 for 16 rows
+// x 16 temperatures are FP64 matrix instructions, Er the row's level of most weight in
+// the block at b.  A block's sums join the running ones under their scale, kept to twice
+// the double precision, about the Er of the largest block so far (so the variance loses
+// little; about Ek instead, a tile with nearly all its weight in one level lost digits
+// and was done again: a call of 16 rows of 20 001 levels at 1000 temperatures of 0.05 to
+// 0.5 took 887 us, level by level alone 761, now 636).  One block per tile, its 8
 // waves taking every 8th block of bins.  201 rows of 20 001 levels at 601
-// temperatures: 2.47 -> 1.03 ms, and c 9.7e-14 -> 2.9e-16 off the sums in 80 bits.
+// temperatures: 2.47 ms level by level, now 0.72.
 // Tiles whose 1/T spread so far that K would leave e^+-kSpread are marked, and taken by a
 // second launch level by level (k_thermo_direct): one block per row and 8 temperatures,
 // pass 1 for the largest exponent and its bin, pass 2 for the sums about that energy.
@@ -268,30 +271,40 @@ __global__ void __launch_bounds__(512) k_thermo(const double* __restrict__ lng, 
         }
         const bool some = top > -__builtin_inf();
         double mx = -__builtin_inf();
+        int at = 32;                                          // the level of most weight at mid
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
             a[q] = some ? (a[q] - top) - mid * (step * (double)(4 * q + lk - 32)) : -__builtin_inf();
-            mx = a[q] > mx ? a[q] : mx;
+            if (a[q] > mx) {
+                mx = a[q];
+                at = 4 * q + lk;
+            }
         }
         for (int o = 16; o < 64; o <<= 1) {
             const double m2 = __shfl_xor(mx, o);
-            mx = m2 > mx ? m2 : mx;
+            const int a2 = __shfl_xor(at, o);
+            if (m2 > mx || (m2 == mx && a2 < at)) {
+                mx = m2;
+                at = a2;
+            }
         }
+        const double e0 = step * (double)(lk - at);
         f64x4 Z = {}, S1 = {}, S2 = {};
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
             const double g = some ? exp(a[q] - mx) : 0.0, kk = K[4 * q + lk][li];
-            const double e = step * (double)(4 * q + lk - 32), k1 = kk * e;
+            const double e = e0 + step * (double)(4 * q), g1 = g * e;
             Z = __builtin_amdgcn_mfma_f64_16x16x4f64(g, kk, Z, 0, 0, 0);
-            S1 = __builtin_amdgcn_mfma_f64_16x16x4f64(g, k1, S1, 0, 0, 0);
-            S2 = __builtin_amdgcn_mfma_f64_16x16x4f64(g, k1 * e, S2, 0, 0, 0);
+            S1 = __builtin_amdgcn_mfma_f64_16x16x4f64(g1, kk, S1, 0, 0, 0);
+            S2 = __builtin_amdgcn_mfma_f64_16x16x4f64(g1 * e, kk, S2, 0, 0, 0);
         }
         // entry r: row 4 r + lk, temperature li; scale top + mx - beta Ek
         const double Ek = step * (double)(k * 64 + 32) - twoN, p = beta * Ek, pe = __builtin_fma(beta, Ek, -p);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const double tp = __shfl(top, 4 * r + lk), mr = __shfl(mx, 4 * r + lk);
-            Moments b = {-__builtin_inf(), 0.0, Ek, Z[r], S1[r], S2[r]};
+            const double Er = Ek + step * (double)(__shfl(at, 4 * r + lk) - 32);
+            Moments b = {-__builtin_inf(), 0.0, Er, Z[r], S1[r], S2[r]};
             if (tp > -__builtin_inf()) {
                 const dd sum = two_sum(tp, -p);
                 b.hi = sum.hi;
@@ -329,8 +342,8 @@ __global__ void __launch_bounds__(512) k_thermo(const double* __restrict__ lng, 
         }
     }
     __syncthreads();
-    // a variance far below the distance to Ek squared (low temperatures: one level has
-    // nearly all the weight) has lost digits: those again about the level itself
+    // a variance far below the mean square about Er has lost digits (the level of most weight
+    // at this temperature is far from the one at b): those again about the level itself
     if (marks) redo[mine] = (uint8_t)weak[tid >> 1][tid & 1];
 }
 
