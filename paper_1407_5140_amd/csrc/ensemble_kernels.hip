@@ -74,14 +74,15 @@ __device__ __forceinline__ double wave_sum(double v)
 
 // Grid (ceil(nT / 8), S).  redo: null for every tile, or k_thermo's mark per tile of 8.
 // A block's waves take every 64 waves-th bin; up to 8 of them while that leaves a wave 4
-// steps of 64 bins and the whole grid fits the device at once: each wave pays about 300
-// cross-lane steps for its sums (4 x 552 temperatures, 513 levels: 91 us a call with one
-// wave, 106 with 8; 20 001 levels: 432 and 207).
+// steps of 64 bins and the grid has at most 2048 waves, 2 to a SIMD: each wave pays about
+// 300 cross-lane steps for its sums (4 x 552 temperatures, 513 levels: 91 us a call with one
+// wave, 106 with 8; 20 001 levels: 432 and 207.  With up to 8192 waves, 2 x 10 000
+// temperatures and 513 levels took 1.14 times as long as with one wave to a block).
 constexpr int kDirectWaves = 8;
 inline int direct_threads(int S, int nT, int W)
 {
     int w = 1;
-    while (w < kDirectWaves && W >= 512 * w && (int64_t)S * ((nT + kThermoT - 1) / kThermoT) * w * 2 <= 8192) w *= 2;
+    while (w < kDirectWaves && W >= 512 * w && (int64_t)S * ((nT + kThermoT - 1) / kThermoT) * w * 2 <= 2048) w *= 2;
     return 64 * w;
 }
 __global__ void __launch_bounds__(64 * kDirectWaves) k_thermo_direct(const double* __restrict__ lng, int W, int model, int N,
@@ -133,16 +134,16 @@ __global__ void __launch_bounds__(64 * kDirectWaves) k_thermo_direct(const doubl
                 arg[i] = a2;
             }
         }
-        if (lane == 0) {
+        if (waves > 1 && lane == 0) {
             part[wave][0][i] = mx[i];
             at[wave][i] = arg[i];
         }
     }
-    __syncthreads();
+    if (waves > 1) __syncthreads();
     double Em[n], Z[n], S1[n], S2[n];
 #pragma unroll
     for (int i = 0; i < n; ++i) {
-        for (int w = 0; w < waves; ++w) {
+        for (int w = 0; w < waves && waves > 1; ++w) {
             const double m2 = part[w][0][i];
             const int a2 = at[w][i];
             if (m2 > mx[i] || (m2 == mx[i] && a2 < arg[i])) {
@@ -153,7 +154,7 @@ __global__ void __launch_bounds__(64 * kDirectWaves) k_thermo_direct(const doubl
         Em[i] = model == 0 ? 4.0 * arg[i] - twoN : (double)arg[i] - twoN;
         Z[i] = S1[i] = S2[i] = 0.0;
     }
-    __syncthreads();
+    if (waves > 1) __syncthreads();
     for (int b = threadIdx.x; b < W; b += blockDim.x) {
         const double v = row[b];
         if (!(v > -__builtin_inf())) continue;
@@ -174,24 +175,27 @@ __global__ void __launch_bounds__(64 * kDirectWaves) k_thermo_direct(const doubl
         Z[i] = wave_sum(Z[i]);
         S1[i] = wave_sum(S1[i]);
         S2[i] = wave_sum(S2[i]);
-        if (lane == 0) {
+        if (waves > 1 && lane == 0) {
             part[wave][0][i] = Z[i];
             part[wave][1][i] = S1[i];
             part[wave][2][i] = S2[i];
         }
     }
-    __syncthreads();
+    if (waves > 1) __syncthreads();
     if (threadIdx.x < nt) {
         double zz = 0, s1 = 0, s2 = 0, em = 0, m = 0;
 #pragma unroll
         for (int i = 0; i < n; ++i)
             if (i == lane) {
-                em = Em[i]; m = mx[i];
+                zz = Z[i]; s1 = S1[i]; s2 = S2[i]; em = Em[i]; m = mx[i];
             }
-        for (int w = 0; w < waves; ++w) {
-            zz += part[w][0][lane];
-            s1 += part[w][1][lane];
-            s2 += part[w][2][lane];
+        if (waves > 1) {
+            zz = s1 = s2 = 0;
+            for (int w = 0; w < waves; ++w) {
+                zz += part[w][0][lane];
+                s1 += part[w][1][lane];
+                s2 += part[w][2][lane];
+            }
         }
         const double t = T[lane], mean = s1 / zz;
         const size_t o = (size_t)s * nT + t0 + lane;
