@@ -151,6 +151,7 @@ struct HostInst {
 
 struct rewl_handle {
     int device = 0;             // the device current at creation (owns every buffer)
+    int n_cu = 1;
     hipStream_t stream = nullptr;
     bool own_stream = false;
     int n = 0;
@@ -568,6 +569,7 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
         return fail(REWL_E_INVALID, "map_log2 must be 0 (auto) or in [6, 12]");
     rewl_handle* H = new rewl_handle();
     H->device = dev;
+    H->n_cu = n_cu;
     if (tune) H->tune = *tune;
     if (H->tune.poll_every <= 0) H->tune.poll_every = 8;
     H->persist = H->tune.persistent || H->tune.sweep_kind == REWL_SWEEP_AUTO;
@@ -1092,7 +1094,7 @@ rewl_status rewl_concat(rewl_handle* H, int32_t i, double* out_lng, int32_t* joi
     HIP_TRY(d_shift.alloc((size_t)hi.h * 8));
     HIP_TRY(d_join.alloc((size_t)std::max(hi.h - 1, 1) * 4));
     HIP_TRY(d_status.alloc(4));
-    hipLaunchKernelGGL(k_concat, dim3(1), dim3(kConcatThreads), 0, H->stream, H->d_insts, i, hi.dev.base,
+    hipLaunchKernelGGL(k_concat<4>, dim3(1), dim3(kConcatThreads), 0, H->stream, H->d_insts, i, hi.dev.base,
                        d_out.as<double>(), d_join.as<int32_t>(), d_shift.as<double>(), d_status.as<int32_t>());
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipMemcpyAsync(out_lng, d_out.p, (size_t)hi.W * 8, hipMemcpyDeviceToHost, H->stream);
@@ -1161,7 +1163,7 @@ rewl_status rewl_concat_noalloc(rewl_handle* H, int32_t i, double* out_lng, int3
     int32_t* d_status = (int32_t*)(base + off_status);
     int32_t status = 0;
     // k_concat writes every entry it later reads (status and shift[0] first)
-    hipLaunchKernelGGL(k_concat, dim3(1), dim3(kConcatThreads), 0, H->stream, H->d_insts, i, hi.dev.base, d_out, d_join,
+    hipLaunchKernelGGL(k_concat<4>, dim3(1), dim3(kConcatThreads), 0, H->stream, H->d_insts, i, hi.dev.base, d_out, d_join,
                        d_shift, d_status);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(out_lng, d_out, (size_t)hi.W * 8, hipMemcpyDeviceToHost, H->stream));
@@ -1213,8 +1215,9 @@ rewl_status rewl_ensemble(rewl_handle* H, const int32_t* runs, int32_t n, int32_
                        d_ptrs.as<const double*>(), n, h, WB, (uint32_t)seed, (uint32_t)(seed >> 32),
                        d_mean.as<double>());
     HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_concat, dim3((unsigned)rows), dim3(kConcatThreads), 0, H->stream, H->d_insts, runs[0],
-                       d_mean.as<double>(), d_out.as<double>(), d_join.as<int32_t>(),
+    const int threads = concat_threads((int64_t)rows, H->n_cu);
+    hipLaunchKernelGGL(threads == kConcatThreads ? k_concat<4> : k_concat<1>, dim3((unsigned)rows), dim3(threads), 0,
+                       H->stream, H->d_insts, runs[0], d_mean.as<double>(), d_out.as<double>(), d_join.as<int32_t>(),
                        d_shift.as<double>(), d_status.as<int32_t>());
     HIP_TRY(hipGetLastError());
     HIP_TRY(copy_out(H->stream, out_lng, d_out.p, out_b));

@@ -1245,6 +1245,7 @@ __global__ void k_init(const Inst* __restrict__ insts, const int32_t* __restrict
 // ascend), so every wave first searches windows of its own in full, and wave 0 then
 // goes through them in order, searching again only where the join found lies below
 // that end.  (76 overlaps of 751 bins one after the other took 770 us for 201 sets, now 310.)
+template <int U>
 __device__ int join_of(const Inst& I, const double* __restrict__ fa, const double* __restrict__ fb, int loa, int lob,
                        int hia, int d, int first)
 {
@@ -1253,11 +1254,11 @@ __device__ int join_of(const Inst& I, const double* __restrict__ fa, const doubl
     double best = __builtin_inf();
     int bestb = -1;
     const int last = hia - 2 * d;              // every load below stays inside both pieces
-    for (int b0 = first; b0 <= last; b0 += 4 * 64) {
-        bool ok[4];
-        double diff[4];
+    for (int b0 = first; b0 <= last; b0 += U * 64) {
+        bool ok[U];
+        double diff[U];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {          // four at a time: one wait for all their loads
+        for (int u = 0; u < U; ++u) {          // U at a time: one wait for all their loads
             const int b = b0 + 64 * u + lane, bc = b < last ? b : last, ia = bc - loa, ib = bc - lob;
             ok[u] = b <= last && (mk[bc] & mk[bc - d] & mk[bc + d] & mk[bc - 2 * d] & mk[bc + 2 * d]);
             const double na = ((fa[ia - 2 * d] - 8.0 * fa[ia - d]) + 8.0 * fa[ia + d]) - fa[ia + 2 * d];
@@ -1265,7 +1266,7 @@ __device__ int join_of(const Inst& I, const double* __restrict__ fa, const doubl
             diff[u] = fabs(na / (12.0 * d) - nbv / (12.0 * d));
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < U; ++u)
             if (ok[u] && (bestb < 0 || diff[u] < best)) {
                 best = diff[u];
                 bestb = b0 + 64 * u + lane;
@@ -1282,7 +1283,18 @@ __device__ int join_of(const Inst& I, const double* __restrict__ fa, const doubl
     return bestb;
 }
 
+// Threads of a block for so many rows on n_cu CUs, U windows' loads at a time.  Alone on its
+// CU a block is fastest with 16 waves and four loads under way (94 registers); of more rows
+// as many blocks share a CU as its 32 waves allow with one load under way (54 registers).
+// Kernel, us, with 1024 threads and U = 4 / so: 1001 rows of Ising L=16, 8 windows 64 / 20,
+// L=64, 16 windows 259 / 158, Potts L=100, 77 windows 1494 / 1040; 4001 rows 234 / 42 and
+// 1061 / 545; 201 rows of Potts L=100 353 / 451 (512 threads).
 constexpr int kConcatThreads = 1024;
+inline int concat_threads(int64_t rows, int n_cu)
+{
+    return rows <= n_cu ? kConcatThreads : rows <= 4 * (int64_t)n_cu ? 512 : rows <= 8 * (int64_t)n_cu ? 256 : 128;
+}
+template <int U>
 __global__ void __launch_bounds__(kConcatThreads) k_concat(const Inst* __restrict__ insts, int inst,
                                                            const double* __restrict__ pieces,
                                                            double* __restrict__ out,
@@ -1302,11 +1314,11 @@ __global__ void __launch_bounds__(kConcatThreads) k_concat(const Inst* __restric
         const int d = (I.hi[a] - I.lo[a + 1] + 1) / 8;
         return d < 1 ? 1 : (d > 10 ? 10 : d);
     };
-    for (int a = tid >> 6; a + 1 < h; a += kConcatThreads / 64) {
+    for (int a = tid >> 6; a + 1 < h; a += (int)(blockDim.x >> 6)) {
         const double* fa = pieces + (size_t)a * WB;
         const double* fb = pieces + (size_t)(a + 1) * WB;
         const int d = stencil(a), loa = I.lo[a], lob = I.lo[a + 1];
-        const int bs = join_of(I, fa, fb, loa, lob, I.hi[a], d, lob + 2 * d);
+        const int bs = join_of<U>(I, fa, fb, loa, lob, I.hi[a], d, lob + 2 * d);
         if ((tid & 63) == 0) {
             join[a] = bs;
             shift[a + 1] = bs < 0 ? 0.0 : fa[bs - loa] - fb[bs - lob];
@@ -1332,7 +1344,7 @@ __global__ void __launch_bounds__(kConcatThreads) k_concat(const Inst* __restric
                     const double* fa = pieces + (size_t)a * WB;
                     const double* fb = pieces + (size_t)(a + 1) * WB;
                     const int loa = I.lo[a], lob = I.lo[a + 1];
-                    bs = __builtin_amdgcn_readfirstlane(join_of(I, fa, fb, loa, lob, I.hi[a], stencil(a), first));
+                    bs = __builtin_amdgcn_readfirstlane(join_of<U>(I, fa, fb, loa, lob, I.hi[a], stencil(a), first));
                     step = bs < 0 ? 0.0 : fa[bs - loa] - fb[bs - lob];
                 }
                 if (bs < 0) {                  // no valid join: report, keep indices inside

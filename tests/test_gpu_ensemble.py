@@ -238,6 +238,32 @@ def test_ensemble_joins_of_many_overlaps(rw, L, h, overlap):
     assert np.max(np.abs(grows[:, ok] - orows[:, ok])) < 1e-9
 
 
+@pytest.mark.parametrize("R", [255, 256, 1023, 1024, 2047, 2048])
+@pytest.mark.parametrize("L,h", [(8, 1), (16, 9), (24, 33)])
+def test_ensemble_of_many_rows(rw, L, h, R):
+    """On both sides of the rows per CU at which the joining's blocks get smaller (256 CUs).
+    Joins exact, of the first rows and of the last."""
+    kws = [dict(model="ising", L=L, n_windows=h, overlap=(9, 10), m=1, kfinal=12, X=100, seed=s) for s in (1, 2)]
+    c = O.make_config(**kws[0])
+    W, (lo, hi), mask = O.n_bins(c), O.layout(c), O.mask_rule(c)
+    rng = np.random.default_rng(h + R)
+    gpu = rw.Rewl([rw.make_config(**kw) for kw in kws])
+    runs = np.zeros((2, h, int((hi - lo).max()) + 1))
+    for j in range(2):
+        t = np.round((L * np.sin(np.pi * np.arange(W) / W) + rng.normal(0, 0.1, W)) * 2.0 ** 16) / 2.0 ** 16
+        gpu.set_initial_lng(t, j)
+        for a in range(h):
+            runs[j, a, : hi[a] - lo[a] + 1] = t[lo[a]: hi[a] + 1]
+    grows, gjoin = gpu.ensemble([0, 1], R=R, seed=9)
+    gpu.close()
+    orows, ojoin = EN.ensemble(c, mask, runs, R=24, seed=9)
+    ok = mask > 0
+    assert np.array_equal(gjoin[:25], ojoin) and np.max(np.abs(grows[:25][:, ok] - orows[:, ok])) < 1e-9
+    last = EN.boot_picks(9, R, h, 2)[R]
+    olast, jlast = EN.concat(c, mask, EN.mean_pieces(runs, last))
+    assert np.array_equal(gjoin[R], jlast) and np.max(np.abs(grows[R][ok] - olast[ok])) < 1e-9
+
+
 def test_ensemble_reports_an_overlap_without_a_join(rw):
     # overlaps of one bin: no five-point stencil fits
     kw = dict(model="ising", L=8, n_windows=4, overlap=(0, 1), m=1, kfinal=8, X=100)
