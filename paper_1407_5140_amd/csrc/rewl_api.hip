@@ -178,7 +178,7 @@ struct rewl_handle {
     int slot_threads = 0;
     size_t max_lds = 0;
     InstCtr* d_ctr = nullptr;
-    InstCtr* h_ctr = nullptr;   // pinned
+    InstCtr* h_ctr = nullptr;   // pinned, with the stage behind it
     char* h_stage = nullptr;    // pinned, kStageBytes: small pieces of state on their way to the host (may be null)
     bool started = false;
     rewl_tune tune{};
@@ -532,7 +532,6 @@ void rewl_destroy(rewl_handle* H)
         if (e) (void)hipEventDestroy(e);
     for (void* p : H->allocs) (void)hipFree(p);
     if (H->h_ctr) (void)hipHostFree(H->h_ctr);
-    if (H->h_stage) (void)hipHostFree(H->h_stage);
     if (H->own_stream && H->stream) (void)hipStreamDestroy(H->stream);
     delete H;
 }
@@ -757,11 +756,13 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
     if ((s = H->alloc(&H->d_queue, 2)) != REWL_OK) return bail(s);
     if (hipMemsetAsync(H->d_queue, 0, 8, H->stream) != hipSuccess)
         return bail(fail(REWL_E_DEVICE, "memset failed"));
-    if (hipHostMalloc((void**)&H->h_ctr, sizeof(InstCtr) * n, hipHostMallocDefault) != hipSuccess)
-        return bail(fail(REWL_E_NOMEM, "hipHostMalloc failed"));
-    if (hipHostMalloc((void**)&H->h_stage, kStageBytes, hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();                             // the pieces are copied one by one then
-        H->h_stage = nullptr;
+    // the counters and the stage behind them in one piece (each call costs about 30 us)
+    if (hipHostMalloc((void**)&H->h_ctr, sizeof(InstCtr) * n + kStageBytes, hipHostMallocDefault) == hipSuccess) {
+        H->h_stage = (char*)(H->h_ctr + n);
+    } else {
+        (void)hipGetLastError();                             // without a stage: pieces copied one by one
+        if (hipHostMalloc((void**)&H->h_ctr, sizeof(InstCtr) * n, hipHostMallocDefault) != hipSuccess)
+            return bail(fail(REWL_E_NOMEM, "hipHostMalloc failed"));
     }
     if (hipMemsetAsync(H->d_ctr, 0, sizeof(InstCtr) * n, H->stream) != hipSuccess)
         return bail(fail(REWL_E_DEVICE, "memset failed"));
@@ -785,10 +786,12 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
     if ((s = H->alloc(&H->d_insts, n)) != REWL_OK) return bail(s);
     if ((s = H->alloc(&H->d_tiles, tiles.size())) != REWL_OK) return bail(s);
     if ((s = H->alloc(&H->d_wtiles, wtiles.size())) != REWL_OK) return bail(s);
-    if ((s = H->alloc(&H->d_wtmp, H->norder)) != REWL_OK) return bail(s);
-    if ((s = H->alloc(&H->d_wcost, H->norder)) != REWL_OK) return bail(s);
-    if (hipMemsetAsync(H->d_wcost, 0, (size_t)std::max(H->norder, 1) * 4, H->stream) != hipSuccess)
-        return bail(fail(REWL_E_DEVICE, "memset failed"));
+    if (H->norder > 0) {
+        if ((s = H->alloc(&H->d_wtmp, H->norder)) != REWL_OK) return bail(s);
+        if ((s = H->alloc(&H->d_wcost, H->norder)) != REWL_OK) return bail(s);
+        if (hipMemsetAsync(H->d_wcost, 0, (size_t)H->norder * 4, H->stream) != hipSuccess)
+            return bail(fail(REWL_E_DEVICE, "memset failed"));
+    }
     if ((s = H->alloc(&H->d_merge, merges.size())) != REWL_OK) return bail(s);
     if ((s = H->alloc(&H->d_exch_start, exch_start.size())) != REWL_OK) return bail(s);
     if ((s = H->alloc(&H->d_slot_start, slot_start.size())) != REWL_OK) return bail(s);
