@@ -113,7 +113,8 @@ typedef struct {
     int32_t poll_every;         /* intervals between host checks of the done flags      */
     int32_t sweep_kind;         /* REWL_SWEEP_*, applied to every instance that allows it */
     int32_t lds_target_kb;      /* LANE: cap on a tile's LDS (sets walkers per block and
-                                   so blocks per CU); 0 = the device limit               */
+                                   so blocks per CU); 0 = the device limit, 40 KB under
+                                   REWL_SWEEP_AUTO                                       */
     int32_t autotune;           /* 1: time candidate variants, LDS targets, the
                                    persistent lane sweep, table placements and site-map
                                    sizes on the real batch for two intervals at
@@ -127,7 +128,8 @@ typedef struct {
     int32_t persistent;         /* LANE sweep: 1 = a grid of as many blocks as the GPU
                                    holds at once, each taking tiles (longest first) from
                                    a device-side queue until none is left; 0 = one
-                                   block per tile, handed out by the hardware          */
+                                   block per tile, handed out by the hardware (under
+                                   REWL_SWEEP_AUTO the queue either way)               */
     int32_t map_log2;           /* WAVE sweep: at most 2^map_log2 site-map entries per
                                    walker (6..12); 0 = auto.  The map marks which
                                    attempts of a 64-attempt chunk lie in one another's
@@ -322,7 +324,8 @@ rewl_status rewl_restore(rewl_handle* h, const void* buf, size_t len);
 void rewl_destroy(rewl_handle* h);
 const char* rewl_last_error(void);
 
-/* The tuning in effect (after autotuning, the winner). */
+/* The tuning in effect: after autotuning the winner; under REWL_SWEEP_AUTO with
+ * instances on the LANE sweep, persistent and lds_target_kb as they are used. */
 rewl_status rewl_get_tune(rewl_handle* h, rewl_tune* out);
 
 /* Number of instances, and for one instance the sweep variant chosen

@@ -161,7 +161,6 @@ struct rewl_handle {
     Tile* d_tiles = nullptr;
     int ntiles = 0;
     int32_t* d_queue = nullptr; // tile queue of the persistent lane sweep
-    bool persist = false;       // asked for, or the library's own choice of variant
     int persist_grid = 0;       // its blocks: as many as the GPU holds at once
     Tile* d_wtiles = nullptr;
     int nwtiles = 0;
@@ -255,7 +254,7 @@ rewl_status enqueue_interval(rewl_handle* H, bool time_it)
 {
     if (time_it) HIP_TRY(hipEventRecord(H->ev[0], H->stream));
     if (time_it) HIP_TRY(hipEventRecord(H->ev[1], H->stream));
-    if (H->ntiles > 0 && H->persist)
+    if (H->ntiles > 0 && H->tune.persistent)
         hipLaunchKernelGGL(k_sweep_persist, dim3(H->persist_grid), dim3(128), H->max_lds, H->stream, H->d_insts,
                            H->d_tiles, H->ntiles, H->d_queue);
     else if (H->ntiles > 0)
@@ -571,7 +570,6 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
     H->n_cu = n_cu;
     if (tune) H->tune = *tune;
     if (H->tune.poll_every <= 0) H->tune.poll_every = 8;
-    H->persist = H->tune.persistent || H->tune.sweep_kind == REWL_SWEEP_AUTO;
     const double band = H->tune.guard_band_log2 ? std::ldexp(1.0, H->tune.guard_band_log2) : kBand;
     H->n = n;
     H->inst.resize(n);
@@ -605,7 +603,7 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
     // instances, 65 280 walkers: all lane 11.3, all wave 9.5, by this rule 9.6.  Its lane tiles
     // are capped at 40 KB (Ising L=16, 131 072 walkers: 10.3 at 53 KB, 8.8) and handed out by
     // the queue (11.5 to 10.2 there).
-    constexpr size_t kLaneBytes = 1792, kLaneTile = size_t(40) << 10;
+    constexpr size_t kLaneBytes = 1792, kLaneTile = 40;
     constexpr int64_t kLaneWalkers = 16384;
     int64_t total_walkers = 0, small_walkers = 0;
     std::vector<size_t> lane_bytes(n);
@@ -657,7 +655,7 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
             while (wpb * 2 <= std::min(want, std::min(64, hi.m))) wpb *= 2;
             size_t cap = (size_t)lds_limit;
             if (H->tune.lds_target_kb > 0) cap = std::min(cap, (size_t)H->tune.lds_target_kb * 1024);
-            else if (H->tune.sweep_kind == REWL_SWEEP_AUTO) cap = std::min(cap, kLaneTile);
+            else if (H->tune.sweep_kind == REWL_SWEEP_AUTO) cap = std::min(cap, kLaneTile << 10);
             while (wpb > 1 && sweep_lds_bytes(c.model, c.L, hi.wpr, hi.WB, wpb) > cap) wpb /= 2;
             hi.wpb = wpb;
             hi.lds = sweep_lds_bytes(c.model, c.L, hi.wpr, hi.WB, wpb);
@@ -778,6 +776,10 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
         return a.N > b.N;
     });
     H->ntiles = (int)tiles.size();
+    if (H->ntiles > 0 && H->tune.sweep_kind == REWL_SWEEP_AUTO) {         // the tuning in effect
+        H->tune.persistent = 1;
+        if (H->tune.lds_target_kb <= 0) H->tune.lds_target_kb = (int)kLaneTile;
+    }
     H->nwtiles = (int)wtiles.size();
     H->norder = H->nwtiles > n_cu ? H->nwtiles : 0;
     H->nmerge = (int)merges.size();

@@ -115,3 +115,20 @@ def test_lane_tables_that_fill_the_lds(rw, kind, short, kw):
     gpu.close()
     assert info["sweep_kind"] == "lane" and info["walkers_per_block"] == 1 and info["lds_bytes"] <= 163840
     lockstep(rw, kw, t, (1, 2))
+
+
+@pytest.mark.parametrize("instances,lds_kb,effect", [(2, 0, (0, 0)), (2, 53, (0, 53)), (64, 0, (1, 40)), (64, 53, (1, 53))])
+def test_tune_reports_what_auto_uses(rw, instances, lds_kb, effect):
+    import bench
+    cfgs = [rw.make_config(model="ising", L=6, n_windows=2, m=256, kfinal=12, X=50, seed=s) for s in range(instances)]
+    gpu = rw.Rewl(cfgs, tune=rw.make_tune("auto", lds_target_kb=lds_kb))
+    tune, info = gpu.tune(), gpu.info()
+    assert (tune["persistent"], tune["lds_target_kb"]) == effect and tune["sweep_kind"] == 0
+    assert bench.sweep_kernel(info, tune) == ("k_sweep_persist" if instances == 64 else "k_sweep_wave")
+    gpu.run(2)
+    again = rw.Rewl(cfgs, tune=rw.rewl_tune(**tune))
+    again.run(2)
+    assert again.tune() == tune and again.info() == info
+    assert_same(gpu.state(5 % instances), again.state(5 % instances), "created with the tuning in effect")
+    gpu.close()
+    again.close()
