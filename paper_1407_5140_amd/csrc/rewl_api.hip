@@ -160,6 +160,8 @@ struct rewl_handle {
     Inst* d_insts = nullptr;
     Tile* d_tiles = nullptr;
     int ntiles = 0;
+    int nfar = 0;               // behind them in d_tiles: tiles with their draws in device memory
+    size_t max_lds_far = 0;
     int32_t* d_queue = nullptr; // tile queue of the persistent lane sweep
     int persist_grid = 0;       // its blocks: as many as the GPU holds at once
     Tile* d_wtiles = nullptr;
@@ -260,6 +262,9 @@ rewl_status enqueue_interval(rewl_handle* H, bool time_it)
     else if (H->ntiles > 0)
         hipLaunchKernelGGL(k_sweep, dim3(H->ntiles), dim3(128), H->max_lds, H->stream, H->d_insts,
                            H->d_tiles, H->ntiles);
+    if (H->nfar > 0)
+        hipLaunchKernelGGL(k_sweep_far, dim3(H->nfar), dim3(128), H->max_lds_far, H->stream, H->d_insts,
+                           H->d_tiles + H->ntiles);
     if (H->nwtiles > 0)
         hipLaunchKernelGGL(k_sweep_wave, dim3(H->nwtiles), dim3(H->wave_threads), H->max_lds_wave,
                            H->stream, H->d_insts, H->d_wtiles, H->norder ? H->d_wcost : nullptr);
@@ -663,7 +668,8 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
                 hi.far_draws = true;
                 hi.lds = sweep_lds_bytes(c.model, c.L, hi.wpr, hi.WB, wpb, true);
             }
-            H->max_lds = std::max(H->max_lds, hi.lds);
+            size_t& most = hi.far_draws ? H->max_lds_far : H->max_lds;
+            most = std::max(most, hi.lds);
         } else {
             WavePlan best;
             if (!plan_wave(c.model, c.L, hi.N, hi.WB, hi.m, total_walkers, H->tune, lds_limit, n_cu, wave_cap, &best))
@@ -772,10 +778,12 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
     // persistent sweep hands them out in this order, the plain launch in block order
     std::stable_sort(tiles.begin(), tiles.end(), [&](const Tile& x, const Tile& y) {
         const HostInst &a = H->inst[x.inst], &b = H->inst[y.inst];
+        if (a.far_draws != b.far_draws) return b.far_draws;
         if (a.cfg.model != b.cfg.model) return a.cfg.model > b.cfg.model;
         return a.N > b.N;
     });
-    H->ntiles = (int)tiles.size();
+    H->nfar = (int)std::count_if(tiles.begin(), tiles.end(), [&](const Tile& t) { return H->inst[t.inst].far_draws; });
+    H->ntiles = (int)tiles.size() - H->nfar;
     if (H->ntiles > 0 && H->tune.sweep_kind == REWL_SWEEP_AUTO) {         // the tuning in effect
         H->tune.persistent = 1;
         if (H->tune.lds_target_kb <= 0) H->tune.lds_target_kb = (int)kLaneTile;
@@ -813,6 +821,8 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
                             (int)std::max<size_t>(H->max_lds, 1)) != hipSuccess ||
         hipFuncSetAttribute((const void*)k_sweep_persist, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)std::max<size_t>(H->max_lds, 1)) != hipSuccess ||
+        hipFuncSetAttribute((const void*)k_sweep_far, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)std::max<size_t>(H->max_lds_far, 1)) != hipSuccess ||
         hipFuncSetAttribute((const void*)k_sweep_wave, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)std::max<size_t>(H->max_lds_wave, 1)) != hipSuccess)
         return bail(fail(REWL_E_DEVICE, "cannot raise the dynamic LDS limit"));

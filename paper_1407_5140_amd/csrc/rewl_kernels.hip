@@ -339,19 +339,17 @@ __device__ void sweep_tile(const Inst& I, const Tile& tile, char* smem)
     }
 }
 
+template <bool FAR>
 __device__ __forceinline__ void sweep_one_tile(const Inst* __restrict__ insts, const Tile& tile, char* smem)
 {
     const Inst& I = insts[tile.inst];
     if (I.ctr->all_done) return;
-    if (__builtin_expect(I.draws != nullptr, 0)) {
+    if (I.model == 0) {
         // (Ising rows of one word have at most 4097 levels, 48 KB of tables)
-        if (I.model == 0) sweep_tile<0, 2, true>(I, tile, smem);
-        else sweep_tile<1, 1, true>(I, tile, smem);
-    } else if (I.model == 0) {
-        if (I.wpr == 1) sweep_tile<0, 1, false>(I, tile, smem);
-        else sweep_tile<0, 2, false>(I, tile, smem);
+        if (!FAR && I.wpr == 1) sweep_tile<0, 1, false>(I, tile, smem);
+        else sweep_tile<0, 2, FAR>(I, tile, smem);
     } else {
-        sweep_tile<1, 1, false>(I, tile, smem);
+        sweep_tile<1, 1, FAR>(I, tile, smem);
     }
 }
 
@@ -359,7 +357,14 @@ __global__ void __launch_bounds__(128) k_sweep(const Inst* __restrict__ insts,
                                               const Tile* __restrict__ tiles, int ntiles)
 {
     extern __shared__ __align__(16) char smem[];
-    sweep_one_tile(insts, tiles[blockIdx.x], smem);
+    sweep_one_tile<false>(insts, tiles[blockIdx.x], smem);
+}
+
+// Tiles of one walker whose draws lie in device memory.
+__global__ void __launch_bounds__(128) k_sweep_far(const Inst* __restrict__ insts, const Tile* __restrict__ tiles)
+{
+    extern __shared__ __align__(16) char smem[];
+    sweep_one_tile<true>(insts, tiles[blockIdx.x], smem);
 }
 
 // Persistent form: a grid sized to the blocks the GPU holds at once; each block
@@ -378,7 +383,7 @@ __global__ void __launch_bounds__(128) k_sweep_persist(const Inst* __restrict__ 
         const int t = next;
         __syncthreads();
         if (t >= ntiles) break;             // block-uniform: every wave of the grid ends here
-        sweep_one_tile(insts, tiles[t], smem);
+        sweep_one_tile<false>(insts, tiles[t], smem);
         __syncthreads();                    // the tile's LDS is free before the next one is staged
     }
 }

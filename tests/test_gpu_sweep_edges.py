@@ -132,3 +132,18 @@ def test_tune_reports_what_auto_uses(rw, instances, lds_kb, effect):
     assert_same(gpu.state(5 % instances), again.state(5 % instances), "created with the tuning in effect")
     gpu.close()
     again.close()
+
+
+def test_lane_tiles_of_both_kinds_in_a_batch(rw):
+    """Tiles with their draws in device memory beside ones with them in the LDS."""
+    big = dict(model="potts", q=10, L=100, n_windows=2, m=2, windows=([0, 12781], [12810, 20000]))
+    kws = [dict(kw, kfinal=12, X=300, seed=s) for s, kw in enumerate([dict(model="ising", L=8, n_windows=4, m=4), big, dict(model="potts", q=4, L=9, n_windows=2, m=8), big])]
+    for persistent in (0, 1):
+        gpu = rw.Rewl([rw.make_config(**kw) for kw in kws], tune=rw.make_tune("lane", walkers_per_block=4, persistent=persistent))
+        assert gpu.info(1)["lds_bytes"] > 163840 - 128
+        gpu.run(3)
+        for i, kw in enumerate(kws):
+            orc = O.Sim(O.make_config(**kw))
+            orc.run(3)
+            assert_same(gpu.state(i), orc.state(), f"instance {i}")
+        gpu.close()
