@@ -90,8 +90,10 @@ enum { REWL_FLAT_MEAN = 0, REWL_FLAT_VISITS = 1 };
  * the next 64 attempts (suits few walkers and large lattices; falls back to LANE
  * where one walker's wave tables do not fit the LDS).  AUTO: WAVE, but LANE (as a
  * persistent grid, tiles of at most 40 KB unless lds_target_kb says otherwise) for
- * the instances whose LANE tables take at most 1.75 KB per walker if those have
- * 16384 walkers or more in all.  Both give bit-identical results.                */
+ * the instances whose LANE tables take at most 1.75 KB per walker and whose tiles
+ * hold 16 walkers (8 on lattices of at most 100 sites, Potts 36), if those have
+ * enough walkers in all: 16384 of up to 100 sites (Potts 64), growing to 30720 with
+ * the sites.  Both give bit-identical results.                                    */
 enum { REWL_SWEEP_AUTO = 0, REWL_SWEEP_LANE = 1, REWL_SWEEP_WAVE = 2 };
 
 /* Where the WAVE sweep keeps a walker's counts while it runs.  LDS: a 32-bit copy

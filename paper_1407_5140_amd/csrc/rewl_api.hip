@@ -596,22 +596,39 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
     for (int k = 0; k < 4; ++k)
         if (hipEventCreate(&H->ev[k]) != hipSuccess) return bail(fail(REWL_E_DEVICE, "hipEventCreate failed"));
 
-    // AUTO's choice between the variants, per instance.  The wave variant makes about 6
-    // walkers' intervals of 10^4 attempts per us whatever the lattice; the lane variant is
-    // limited by the walkers whose tables the LDS holds at once (about 0.03 + 0.075 us per
-    // KB of a walker's tables), and an interval takes it 2.9 ms however few they are.  So
-    // it takes the instances of small tables where there are enough of them.  Measured,
-    // ms per interval, lane against wave: Ising L=16 (0.7 KB), 131 072 walkers 8.8 / 22.5,
-    // 32 768 3.4 / 5.9, 16 384 2.6 / 3.1, 8192 2.1 / 1.7; Potts q=10 L=16 (1.2 KB), 131 072
-    // 12.1 / 19.0, 32 768 3.7 / 4.9, 16 384 3.0 / 2.6; Ising L=32, 65 536 7.2 / 9.2; Ising
-    // L=64, 32 768 (2.5 KB) 6.7 / 4.6; Potts q=10 L=32, 32 768 (2.8 KB) 8.3 / 4.0; 64 unequal
-    // instances, 65 280 walkers: all lane 11.3, all wave 9.5, by this rule 9.6.  Its lane tiles
-    // are capped at 40 KB (Ising L=16, 131 072 walkers: 10.3 at 53 KB, 8.8) and handed out by
-    // the queue (11.5 to 10.2 there).
+    // AUTO's choice between the variants, per instance.  An interval of 10^4 attempts takes
+    // the lane variant about 3 ms up to 1024 tiles, whatever they hold (3.5 ms for 2048); the
+    // wave variant's time grows with the walkers, by 0.13 us each on large lattices and 0.28
+    // on the smallest (36 sites: nearly every attempt of a chunk lies in another's
+    // neighbourhood).  So the lane variant takes the instances of small tables whose tiles hold
+    // 16 walkers, or 8 on the smallest lattices, if there are enough of them in all: 16 384 of
+    // up to 100 sites (Potts 64), more of larger lattices.  Measured, ms per interval, lane /
+    // wave.  Tiles of 32: Ising L=8, 12 288 walkers 2.7 / 3.0, 16 384 2.7 / 3.9; L=16 (8 windows)
+    // 16 384 2.6 / 3.1, (32 windows) 16 384 2.7 / 2.6, 24 576 3.4 / 3.9; L=32 (32 windows) 20 480
+    // 3.4 / 2.7, 24 576 3.4 / 3.2, 32 768 3.4 / 4.3; Potts q=10 L=8, 16 384 3.0 / 3.2; L=16 (8
+    // windows) 16 384 3.0 / 2.6, 24 576 3.8 / 3.8, 32 768 3.7 / 5.0; L=24, 24 576 3.8 / 3.0,
+    // 32 768 3.7 / 3.9.  Of 16: Ising L=8, 32 768 3.8 / 7.6; L=32 (16 windows, 1.4 KB a walker)
+    // 24 576 3.4 / 3.6, 65 536 7.3 / 9.3; Potts L=16 32 768 4.1 / 5.0.  Of 8: Ising L=8, 16 384
+    // 3.7 / 3.9, 65 536 11.6 / 14.9; L=16 32 768 6.0 / 5.9; Potts L=8 7.5 / 6.2.  Of 4: Ising L=8,
+    // 32 768 11.6 / 7.6.  Ising L=64, 32 768 (2.5 KB a walker) 6.7 / 4.6.  Lane tiles are capped
+    // at 40 KB (Ising L=16, 131 072 walkers: 10.3 at 53 KB, 8.8) and handed out by the queue (11.5
+    // to 10.2 there).  64 unequal instances, 65 280 walkers: half of them lane 9.6, all wave 9.4.
+    const bool is_auto = H->tune.sweep_kind == REWL_SWEEP_AUTO;
     constexpr size_t kLaneBytes = 1792, kLaneTile = 40;
-    constexpr int64_t kLaneWalkers = 16384;
-    int64_t total_walkers = 0, small_walkers = 0;
-    std::vector<size_t> lane_bytes(n);
+    auto lane_width = [&](const rewl_config& c, int WB) {     // walkers to a tile
+        const int want = H->tune.walkers_per_block > 0 ? H->tune.walkers_per_block : 64;
+        int w = 1;
+        while (w * 2 <= std::min(want, std::min(64, c.walkers_per_window))) w *= 2;
+        size_t cap = (size_t)lds_limit;
+        if (H->tune.lds_target_kb > 0) cap = std::min(cap, (size_t)H->tune.lds_target_kb * 1024);
+        else if (is_auto) cap = std::min(cap, kLaneTile << 10);
+        const int wpr = c.model == 0 ? (c.L + 63) / 64 : 1;
+        while (w > 1 && sweep_lds_bytes(c.model, c.L, wpr, WB, w) > cap) w /= 2;
+        return w;
+    };
+    int64_t total_walkers = 0;
+    double lane_share = 0.0;                                 // of the walkers it takes
+    std::vector<bool> suits_lane(n);
     for (int u = 0; u < n; ++u) {
         const rewl_config& c = cfgs[u];
         const int64_t S = (int64_t)c.n_windows * c.walkers_per_window;
@@ -619,11 +636,14 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
         layout_of(c, lo, hi);
         int WB = 0;
         for (int a = 0; a < c.n_windows; ++a) WB = std::max(WB, hi[a] - lo[a] + 1);
-        lane_bytes[u] = sweep_lds_bytes(c.model, c.L, c.model == 0 ? (c.L + 63) / 64 : 1, WB, 32) / 32;
+        const bool potts = c.model != 0;
+        const int N = c.L * c.L, w = lane_width(c, WB);
+        const size_t bytes = sweep_lds_bytes(c.model, c.L, potts ? 1 : (c.L + 63) / 64, WB, w) / w;
+        suits_lane[u] = bytes <= kLaneBytes && w >= (N <= (potts ? 36 : 100) ? 8 : 16);
         total_walkers += S;
-        if (lane_bytes[u] <= kLaneBytes) small_walkers += S;
+        if (suits_lane[u])
+            lane_share += (double)S / std::min(30720, 16384 + std::max(0, N - (potts ? 64 : 100)) * (potts ? 60 : 7));
     }
-    const bool many_small = small_walkers >= kLaneWalkers;
     for (int i = 0; i < n; ++i) {
         HostInst& hi = H->inst[i];
         hi.cfg = cfgs[i];
@@ -651,22 +671,15 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
             (size_t)lds_limit;
         hi.kind = REWL_SWEEP_LANE;
         if (wave_ok && (H->tune.sweep_kind == REWL_SWEEP_WAVE ||
-                        (H->tune.sweep_kind == REWL_SWEEP_AUTO && !(many_small && lane_bytes[i] <= kLaneBytes))))
+                        (is_auto && !(lane_share >= 1.0 && suits_lane[i]))))
             hi.kind = REWL_SWEEP_WAVE;
         hi.placement = REWL_TABLE_LDS;
         if (hi.kind == REWL_SWEEP_LANE) {
-            int want = H->tune.walkers_per_block > 0 ? H->tune.walkers_per_block : 64;
-            int wpb = 1;
-            while (wpb * 2 <= std::min(want, std::min(64, hi.m))) wpb *= 2;
-            size_t cap = (size_t)lds_limit;
-            if (H->tune.lds_target_kb > 0) cap = std::min(cap, (size_t)H->tune.lds_target_kb * 1024);
-            else if (H->tune.sweep_kind == REWL_SWEEP_AUTO) cap = std::min(cap, kLaneTile << 10);
-            while (wpb > 1 && sweep_lds_bytes(c.model, c.L, hi.wpr, hi.WB, wpb) > cap) wpb /= 2;
-            hi.wpb = wpb;
-            hi.lds = sweep_lds_bytes(c.model, c.L, hi.wpr, hi.WB, wpb);
+            hi.wpb = lane_width(c, hi.WB);
+            hi.lds = sweep_lds_bytes(c.model, c.L, hi.wpr, hi.WB, hi.wpb);
             if (hi.lds > (size_t)lds_limit) {                // one walker: its draws in device memory
                 hi.far_draws = true;
-                hi.lds = sweep_lds_bytes(c.model, c.L, hi.wpr, hi.WB, wpb, true);
+                hi.lds = sweep_lds_bytes(c.model, c.L, hi.wpr, hi.WB, hi.wpb, true);
             }
             size_t& most = hi.far_draws ? H->max_lds_far : H->max_lds;
             most = std::max(most, hi.lds);
@@ -784,7 +797,7 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
     });
     H->nfar = (int)std::count_if(tiles.begin(), tiles.end(), [&](const Tile& t) { return H->inst[t.inst].far_draws; });
     H->ntiles = (int)tiles.size() - H->nfar;
-    if (H->ntiles > 0 && H->tune.sweep_kind == REWL_SWEEP_AUTO) {         // the tuning in effect
+    if (H->ntiles > 0 && is_auto) {                           // the tuning in effect
         H->tune.persistent = 1;
         if (H->tune.lds_target_kb <= 0) H->tune.lds_target_kb = (int)kLaneTile;
     }

@@ -147,3 +147,28 @@ def test_lane_tiles_of_both_kinds_in_a_batch(rw):
             orc.run(3)
             assert_same(gpu.state(i), orc.state(), f"instance {i}")
         gpu.close()
+
+
+@pytest.mark.parametrize("kw,n,lane", [
+    (dict(model="ising", L=8, n_windows=8, m=64), 32, True),                      # 16 384 walkers in tiles of 64
+    (dict(model="ising", L=8, n_windows=8, m=64), 31, False),
+    (dict(model="ising", L=8, n_windows=8, m=8), 256, True),                      # tiles of 8, few sites
+    (dict(model="ising", L=8, n_windows=8, m=4), 512, False),                     # tiles of 4
+    (dict(model="ising", L=16, n_windows=8, m=8), 300, False),                    # tiles of 8, more sites
+    (dict(model="ising", L=16, n_windows=8, m=16), 140, True),                    # tiles of 16, 17 476 walkers needed
+    (dict(model="ising", L=16, n_windows=8, m=16), 136, False),
+    (dict(model="potts", q=10, L=16, n_windows=8, m=64), 54, False),              # 27 904 needed
+    (dict(model="potts", q=10, L=16, n_windows=8, m=64), 55, True),
+    (dict(model="potts", q=10, L=16, n_windows=8, m=1), 4096, False)],            # one walker to a tile
+    ids=lambda v: f"{v['model']}-L{v['L']}-m{v['m']}" if isinstance(v, dict) else str(v))
+def test_autos_choice(rw, kw, n, lane):
+    """The variant that AUTO takes, and the states of the first and last instance."""
+    kws = [dict(kw, kfinal=12, X=70, seed=s) for s in range(n)]
+    gpu = rw.Rewl([rw.make_config(**kw) for kw in kws], tune=rw.make_tune("auto"))
+    assert {gpu.info(i)["sweep_kind"] for i in range(n)} == {"lane" if lane else "wave"}
+    gpu.run(3)
+    for i in (0, n - 1):
+        orc = O.Sim(O.make_config(**kws[i]))
+        orc.run(3)
+        assert_same(gpu.state(i), orc.state(), f"instance {i}")
+    gpu.close()
