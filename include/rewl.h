@@ -344,6 +344,14 @@ rewl_status rewl_info(rewl_handle* h, int32_t instance, int32_t* n_instances, in
  * Philox4x32-10 blocks: in[6 n] = (ctr0..3, key0, key1), out[4 n].               */
 rewl_status rewl_probe_accept(const double* delta, const uint64_t* u53, int32_t n, int32_t* out);
 rewl_status rewl_probe_philox(const uint32_t* in, int32_t n, uint32_t* out);
+/* The FP32 filters of that predicate: for n draws of words zw[2 n] (u53 = (w 2^32 + z)
+ * >> 11) and a guard band, out[4 n]: the bounds lo, hi of the WAVE sweep (below lo the
+ * predicate rejects for certain, above hi it accepts) and hi, lo of the LANE sweep.
+ * rewl_probe_log2: over the n floats of bit patterns first, first + 1, ... (all positive
+ * and normal), the largest |v_log_f32(u) - log2 u| / (2^-23 (1 + |log2 u|)); the
+ * filters rely on 1 at most for 2^-60 <= u <= 1.                                    */
+rewl_status rewl_probe_bounds(const uint32_t* zw, int32_t n, double band, float* out);
+rewl_status rewl_probe_log2(uint32_t first, int64_t n, double* worst);
 
 #ifdef __cplusplus
 }

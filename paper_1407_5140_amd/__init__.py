@@ -111,6 +111,8 @@ _sigs = {
     "rewl_get_tune": ([_vp, _P(rewl_tune)], ctypes.c_int),
     "rewl_probe_accept": ([_vp, _vp, ctypes.c_int32, _vp], ctypes.c_int),
     "rewl_probe_philox": ([_vp, ctypes.c_int32, _vp], ctypes.c_int),
+    "rewl_probe_bounds": ([_vp, ctypes.c_int32, ctypes.c_double, _vp], ctypes.c_int),
+    "rewl_probe_log2": ([ctypes.c_uint32, ctypes.c_int64, _vp], ctypes.c_int),
     # density-of-states network (include/rewl_mlp.h)
     "mlp_last_error": ([], ctypes.c_char_p),
     "mlp_create": ([_vp, _vp, _P(_vp)], ctypes.c_int),
@@ -403,6 +405,21 @@ def rewl_probe_philox(ctr_key: np.ndarray) -> np.ndarray:
     out = np.empty((len(a), 4), np.uint32)
     _check(_lib.rewl_probe_philox(_p(a), len(a), _p(out)), "rewl_probe_philox")
     return out
+
+
+def rewl_probe_bounds(zw: np.ndarray, band: float) -> np.ndarray:
+    """(lo, hi) of the wave sweep and (hi, lo) of the lane sweep for draws (z, w)."""
+    a = np.ascontiguousarray(zw, dtype=np.uint32).reshape(-1, 2)
+    out = np.empty((len(a), 4), np.float32)
+    _check(_lib.rewl_probe_bounds(_p(a), len(a), float(band), _p(out)), "rewl_probe_bounds")
+    return out
+
+
+def rewl_probe_log2(first: int, n: int) -> float:
+    """Largest error of the device's FP32 log2 over n bit patterns, in 2^-23 (1 + |log2 u|)."""
+    worst = ctypes.c_double(0.0)
+    _check(_lib.rewl_probe_log2(int(first), int(n), ctypes.byref(worst)), "rewl_probe_log2")
+    return worst.value
 
 
 # ------------------------------------------------------------ convenience

@@ -1400,6 +1400,34 @@ rewl_status rewl_probe_accept(const double* delta, const uint64_t* u53, int32_t 
     return REWL_OK;
 }
 
+rewl_status rewl_probe_bounds(const uint32_t* zw, int32_t n, double band, float* out)
+{
+    if (!zw || !out || n < 0 || !(band >= 0.0 && band <= 0.25)) return fail(REWL_E_INVALID, "bad arguments");
+    if (n == 0) return REWL_OK;
+    DevBuf d_zw, d_out;
+    HIP_TRY(d_zw.alloc((size_t)n * 8));
+    HIP_TRY(d_out.alloc((size_t)n * 16));
+    HIP_TRY(hipMemcpy(d_zw.p, zw, (size_t)n * 8, hipMemcpyHostToDevice));
+    hipLaunchKernelGGL(k_bounds_probe, dim3((n + 255) / 256), dim3(256), 0, 0, d_zw.as<uint32_t>(), n, band, d_out.as<float>());
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipMemcpy(out, d_out.p, (size_t)n * 16, hipMemcpyDeviceToHost));
+    return REWL_OK;
+}
+
+rewl_status rewl_probe_log2(uint32_t first, int64_t n, double* worst)
+{
+    if (!worst || n < 0 || first < 0x00800000u || (int64_t)first + n > 0x7f800000) return fail(REWL_E_INVALID, "bad arguments");
+    DevBuf d;
+    HIP_TRY(d.alloc(8));
+    HIP_TRY(hipMemset(d.p, 0, 8));
+    if (n > 0)
+        hipLaunchKernelGGL(k_log2_probe, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 4096)), dim3(256), 0, 0, first, n,
+                           d.as<unsigned long long>());
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipMemcpy(worst, d.p, 8, hipMemcpyDeviceToHost));
+    return REWL_OK;
+}
+
 rewl_status rewl_probe_philox(const uint32_t* in, int32_t n, uint32_t* out)
 {
     if (!in || !out || n < 0) return fail(REWL_E_INVALID, "bad arguments");

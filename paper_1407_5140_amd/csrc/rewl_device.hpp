@@ -165,7 +165,8 @@ __device__ __forceinline__ int decide_fast(double delta, double vb, double band)
 // band, so only a delta between them needs the FP64 logarithm (about one attempt
 // in 10^5).  u = u53 2^-53 enters as fma(z, 2^-32, w) 2^-32, off by less than
 // 2^-20 u for w > 0, and v_log_f32 is within 2^-23 (1 + |log2 u|) of log2 u at
-// every float in [2^-60, 1] (all of them compared); the bounds leave 2^-19 + 2^-20 |log u|.  w = 0 leaves every finite delta open.
+// every float in [2^-60, 1] (k_log2_probe compares them all); the bounds leave
+// 2^-19 + 2^-20 |log u|.  w = 0 leaves every finite delta open.
 struct Bound32 {
     float lo, hi;
 };

@@ -1429,6 +1429,31 @@ __global__ void k_accept_probe(const double* __restrict__ delta, const uint64_t*
     }
 }
 
+__global__ void k_bounds_probe(const uint32_t* __restrict__ zw, int n, double band, float* __restrict__ out)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const uint32_t z = zw[2 * i], w = zw[2 * i + 1];
+    const Bound32 b = bounds_of(z, w, (float)band);
+    const float e = kErrLane + (float)band, hi = upper_of(z, w, e);
+    out[4 * i + 0] = b.lo;
+    out[4 * i + 1] = b.hi;
+    out[4 * i + 2] = hi;
+    out[4 * i + 3] = lower_of(hi, e);
+}
+
+// worst: the bits of a non-negative double, whose order is that of the doubles.
+__global__ void k_log2_probe(uint32_t first, int64_t n, unsigned long long* __restrict__ worst)
+{
+    double mx = 0.0;
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const float u = __builtin_bit_cast(float, (uint32_t)(first + (uint32_t)i));
+        const double l = log2((double)u), e = fabs((double)__builtin_amdgcn_logf(u) - l) / (0x1p-23 * (1.0 + fabs(l)));
+        mx = e > mx ? e : mx;
+    }
+    atomicMax(worst, __builtin_bit_cast(unsigned long long, mx));
+}
+
 __global__ void k_philox_probe(const uint32_t* __restrict__ in, int n, uint32_t* __restrict__ out)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
