@@ -60,7 +60,8 @@ rewl_status mlp_get_params(const mlp_handle* h, float* host, size_t n);
 rewl_status mlp_set_params(mlp_handle* h, const float* host, size_t n);
 
 /* Forward pass: y[r] = net(x[r][0..in_dim)) for r < B (host arrays x[B][in_dim],
- * y[B]; any B >= 0, processed in chunks of max_batch rows). */
+ * y[B]; any B >= 0), uploaded in pieces of max_batch rows, or of 65536 if that is
+ * more and hidden <= 1024. */
 rewl_status mlp_infer(mlp_handle* h, const float* x, float* y, int32_t B);
 
 /* Loss (1/B) sum_r (net(x_r) - t_r)^2 and its gradient with respect to the flat

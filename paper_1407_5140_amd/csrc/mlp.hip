@@ -1009,7 +1009,8 @@ rewl_status mlp_set_params(mlp_handle* h, const float* host, size_t n)
     return REWL_OK;
 }
 
-// Forward over host rows x[B][in_dim] -> y[B], in chunks of max_batch rows.
+// Forward over host rows x[B][in_dim] -> y[B], in uploads of cap rows (layer by layer: of
+// max_batch).
 rewl_status mlp_infer(mlp_handle* h, const float* x, float* y, int32_t B)
 {
     if (!h || (B > 0 && (!x || !y)) || B < 0) return mfail(REWL_E_INVALID, "bad arguments");

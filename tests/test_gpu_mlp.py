@@ -312,3 +312,69 @@ def test_adam_steps_of_shapes(rw, shape):
     finally:
         net.close()
         other.close()
+
+
+# Batches whose weight gradients are split into 4, 8 and 16 spans of 256 rows, one per wave
+# of a block of up to 1024 threads, whole and with a last span that is not.
+@pytest.mark.parametrize("shape", [(3, 64, 2), (3, 128, 3)])
+@pytest.mark.parametrize("B", [1024, 970, 2048, 2001, 4096, 4065])
+def test_gradients_of_many_spans(rw, shape, B):
+    net = rw.Mlp(*shape, max_batch=4096, seed=4)
+    try:
+        p = params(*shape, seed=81)
+        net.set_params(p)
+        x, t = rows(B, shape[0], seed=82)
+        pw = device_weights(p, *shape)
+        g, loss = net.grad(x, t)
+        go, sg = grad_sigma(pw, x, t, *shape, samples=64)
+        assert within(g.astype(np.float64), go, sg, k=8.0).all()
+        assert loss == pytest.approx(M.grad(pw, x, t, *shape)[1], rel=1e-2)
+        assert np.array_equal(g, net.grad(x, t)[0])
+    finally:
+        net.close()
+
+
+@pytest.mark.parametrize("batch", [1024, 2048, 4096])
+def test_adam_steps_of_many_spans(rw, batch):
+    # as test_adam_steps_of_shapes: one row repeated, so that every draw of rows is alike
+    shape = (3, 128, 3)
+    net, other = rw.Mlp(*shape, max_batch=4096, seed=2), rw.Mlp(*shape, max_batch=64, seed=9)
+    try:
+        p = params(*shape, seed=91)
+        net.set_params(p)
+        x, t = rows(1, shape[0], seed=92)
+        X, T = np.repeat(x, batch, axis=0), np.repeat(t, batch)
+        lr, m, v, po = 1e-3, np.zeros_like(p), np.zeros_like(p), p.copy()
+        for step in (1, 2):
+            g, _ = net.grad(X, T)
+            net.fit(X, T, steps=1, batch=batch, lr=lr, seed=7)
+            po_new, m, v = M.adam_step(po, g.astype(np.float64), m, v, step, lr)
+            pd = net.params().astype(np.float64)
+            assert np.all(np.abs(pd - po_new) <= 1e-4 * lr + 2 ** -23 * np.abs(po_new))
+            po = pd
+        other.set_params(net.params())
+        xi, _ = rows(50, shape[0], seed=93)
+        assert np.array_equal(net.infer(xi), other.infer(xi))
+    finally:
+        net.close()
+        other.close()
+
+
+@pytest.mark.parametrize("shape,max_batch", [((3, 64, 1), 512), ((3, 1088, 2), 192)])
+def test_inference_in_several_uploads(rw, shape, max_batch):
+    """More rows than one upload takes (65 536, or max_batch layer by layer), with a ragged
+    tail: every row as in a call of its own piece, and those about the seams as the oracle."""
+    step = 65536 if shape[1] <= 1024 else max_batch
+    net = rw.Mlp(*shape, max_batch=max_batch, seed=4)
+    try:
+        p = params(*shape, seed=95)
+        net.set_params(p)
+        x, _ = rows(2 * step + 77, shape[0], seed=96)
+        y = net.infer(x)
+        for at in range(0, len(x), step // 2 + 11):
+            assert np.array_equal(net.infer(x[at: at + step // 2 + 11]), y[at: at + step // 2 + 11])
+        some = np.unique(np.concatenate([np.arange(20), step + np.arange(-20, 20), 2 * step + np.arange(-20, 77)]))
+        yo, sy = forward_sigma(device_weights(p, *shape), x[some], *shape)
+        assert within(y[some].astype(np.float64), yo, sy).all()
+    finally:
+        net.close()
