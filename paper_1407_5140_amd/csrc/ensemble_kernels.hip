@@ -225,7 +225,8 @@ __device__ __forceinline__ void merge(Moments& a, const Moments& b)
     a.E0 = E0;
 }
 
-// Grid (ceil(nT / 16), ceil(S / 16)); every row has a finite level and neither NaN nor +inf.
+// Grid (ceil(nT / 16), ceil(S / 16)).  Rows without a finite level or with NaN or +inf do no
+// harm; what comes out for them is nowhere used (the host looks at the rows meanwhile).
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 __global__ void __launch_bounds__(512) k_thermo(const double* __restrict__ lng, int S, int W, int model, int N,
                                                 const double* __restrict__ T, int nT, uint8_t* __restrict__ redo, double* __restrict__ u,

@@ -706,6 +706,7 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
         d.band = band;
         d.hglobal = hi.placement == REWL_TABLE_DEVICE ? 1 : 0;
         d.mapn = hi.kind == REWL_SWEEP_WAVE ? hi.mapn : 0;
+        // no kernel has this limit any more: it is that of the configurations that are taken
         if ((uint64_t)((c.exchange_interval + 31) / 32 * 32) * hi.S >= (uint64_t(1) << 32))
             return bail(fail(REWL_E_INVALID, "instance " + std::to_string(i) + ": walkers x interval exceeds 2^32 draws"));
         const size_t S = hi.S, h = hi.h, WB = hi.WB;
@@ -1190,7 +1191,7 @@ rewl_status rewl_concat_noalloc(rewl_handle* H, int32_t i, double* out_lng, int3
     int32_t* d_join = (int32_t*)(base + off_join);
     int32_t* d_status = (int32_t*)(base + off_status);
     int32_t status = 0;
-    // k_concat writes every entry it later reads (status and shift[0] first)
+    // k_concat writes every entry that it or the copies below read
     hipLaunchKernelGGL(k_concat<4>, dim3(1), dim3(kConcatThreads), 0, H->stream, H->d_insts, i, hi.dev.base, d_out, d_join,
                        d_shift, d_status);
     HIP_TRY(hipGetLastError());

@@ -208,11 +208,10 @@ struct alignas(16) InstCtr {
     int32_t stopped;    // the interval that finished the run has been counted
     int32_t n_done;     // converged windows
     int32_t err;        // sticky error flags
-    int32_t queue;      // sweep tile queue head
-    int32_t pad;
+    int32_t unused[2];
 };
 constexpr size_t kCtrBytes = 40;
-static_assert(offsetof(InstCtr, pad) + sizeof(int32_t) == kCtrBytes && sizeof(InstCtr) % 16 == 0, "layout of the counters");
+static_assert(offsetof(InstCtr, unused) + 8 == kCtrBytes && sizeof(InstCtr) % 16 == 0, "layout of the counters");
 
 struct Inst {
     // problem

@@ -399,7 +399,6 @@ __global__ void __launch_bounds__(128) k_sweep_persist(const Inst* __restrict__ 
 // site, or M = 2^j < N entries shared by the sites equal modulo M, which only
 // adds attempts to the out-of-date sets, never removes one (so a smaller map
 // trades extra re-evaluations for LDS).
-constexpr int kWaveMapMax = 4096;
 // site-map entries per walker for a lattice of N sites and a cap of 2^map_log2
 // entries (0: 2^12)
 __host__ __device__ inline int wave_map_entries(int N, int map_log2 = 0)
@@ -1133,7 +1132,6 @@ __global__ void k_advance(const Inst* __restrict__ insts, int n_inst, int32_t* _
         c->t += 1;
         if (c->all_done) c->stopped = 1;
     }
-    c->queue = 0;
 }
 
 // -------------------------------------------------------------------- init
