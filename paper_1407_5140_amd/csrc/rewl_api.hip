@@ -162,6 +162,7 @@ struct rewl_handle {
     int ntiles = 0;
     int nfar = 0;               // behind them in d_tiles: tiles with their draws in device memory
     size_t max_lds_far = 0;
+    char* d_draws = nullptr;
     int32_t* d_queue = nullptr; // tile queue of the persistent lane sweep
     int persist_grid = 0;       // its blocks: as many as the GPU holds at once
     Tile* d_wtiles = nullptr;
@@ -264,7 +265,7 @@ rewl_status enqueue_interval(rewl_handle* H, bool time_it)
                            H->d_tiles, H->ntiles);
     if (H->nfar > 0)
         hipLaunchKernelGGL(k_sweep_far, dim3(H->nfar), dim3(128), H->max_lds_far, H->stream, H->d_insts,
-                           H->d_tiles + H->ntiles);
+                           H->d_tiles + H->ntiles, H->d_draws);
     if (H->nwtiles > 0)
         hipLaunchKernelGGL(k_sweep_wave, dim3(H->nwtiles), dim3(H->wave_threads), H->max_lds_wave,
                            H->stream, H->d_insts, H->d_wtiles, H->norder ? H->d_wcost : nullptr);
@@ -724,7 +725,6 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
         if (s == REWL_OK) s = H->alloc(&d.done, h);
         if (s == REWL_OK) s = H->alloc(&d.flat, S);
         if (s == REWL_OK) s = H->alloc(&d.swaps, S);
-        if (s == REWL_OK && hi.far_draws) s = H->alloc(&d.draws, S * 2 * kDrawBytes);
         if (s == REWL_OK) s = H->alloc(&d.ex_prop, h);
         if (s == REWL_OK) s = H->alloc(&d.ex_acc, h);
         if (s == REWL_OK) s = H->alloc(&d.merges, h);
@@ -809,6 +809,7 @@ static rewl_status create_impl(const rewl_config* cfgs, int32_t n, void* hip_str
     H->slot_threads = slot_start.back();
     if ((s = H->alloc(&H->d_insts, n)) != REWL_OK) return bail(s);
     if ((s = H->alloc(&H->d_tiles, tiles.size())) != REWL_OK) return bail(s);
+    if (H->nfar > 0 && (s = H->alloc(&H->d_draws, (size_t)H->nfar * 2 * kDrawBytes)) != REWL_OK) return bail(s);
     if ((s = H->alloc(&H->d_wtiles, wtiles.size())) != REWL_OK) return bail(s);
     if (H->norder > 0) {
         if ((s = H->alloc(&H->d_wtmp, H->norder)) != REWL_OK) return bail(s);

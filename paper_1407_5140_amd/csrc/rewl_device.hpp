@@ -244,8 +244,6 @@ struct Inst {
     double band;        // guard band of the fast acceptance test
     int32_t hglobal;    // wave sweep: counts read from device memory, not an LDS copy
     int32_t mapn;       // wave sweep: site-map entries per walker (N, or a power of two below N)
-    char* draws;        // lane sweep: [S][2 kDrawBytes] where one walker's tables leave the LDS
-                        //         no room for its draws, else null
     InstCtr* ctr;
 };
 

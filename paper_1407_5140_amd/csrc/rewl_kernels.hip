@@ -75,7 +75,7 @@ __device__ __forceinline__ double rld(double v, int l)
 }
 
 template <int MODEL, int WPR, bool FAR>
-__device__ void sweep_tile(const Inst& I, const Tile& tile, char* smem)
+__device__ void sweep_tile(const Inst& I, const Tile& tile, char* smem, char* draws)
 {
     const int a = tile.window, nw = tile.nw, tid = threadIdx.x, lane = tid & 63;
     const bool walks = tid < 64;                                 // wave 0; wave 1 draws
@@ -93,7 +93,7 @@ __device__ void sweep_tile(const Inst& I, const Tile& tile, char* smem)
     typedef uint32_t Draw __attribute__((ext_vector_type(MODEL ? 4 : 2)));
     constexpr int kDraws = kDrawBytes / (int)sizeof(Draw);
     Draw* ring;
-    if constexpr (FAR) ring = (Draw*)(I.draws + (size_t)slot0 * 2 * kDrawBytes);
+    if constexpr (FAR) ring = (Draw*)draws;
     else ring = (Draw*)(latp + (((MODEL == 0 ? (size_t)L * WPR * 8 : (size_t)N) * nw + 15) & ~size_t(15)));
     const int nthr = blockDim.x;
     const int lnw = __builtin_ctz(nw);                           // nw is a power of two
@@ -340,16 +340,16 @@ __device__ void sweep_tile(const Inst& I, const Tile& tile, char* smem)
 }
 
 template <bool FAR>
-__device__ __forceinline__ void sweep_one_tile(const Inst* __restrict__ insts, const Tile& tile, char* smem)
+__device__ __forceinline__ void sweep_one_tile(const Inst* __restrict__ insts, const Tile& tile, char* smem, char* draws)
 {
     const Inst& I = insts[tile.inst];
     if (I.ctr->all_done) return;
     if (I.model == 0) {
         // (Ising rows of one word have at most 4097 levels, 48 KB of tables)
-        if (!FAR && I.wpr == 1) sweep_tile<0, 1, false>(I, tile, smem);
-        else sweep_tile<0, 2, FAR>(I, tile, smem);
+        if (!FAR && I.wpr == 1) sweep_tile<0, 1, false>(I, tile, smem, draws);
+        else sweep_tile<0, 2, FAR>(I, tile, smem, draws);
     } else {
-        sweep_tile<1, 1, FAR>(I, tile, smem);
+        sweep_tile<1, 1, FAR>(I, tile, smem, draws);
     }
 }
 
@@ -357,14 +357,15 @@ __global__ void __launch_bounds__(128) k_sweep(const Inst* __restrict__ insts,
                                               const Tile* __restrict__ tiles, int ntiles)
 {
     extern __shared__ __align__(16) char smem[];
-    sweep_one_tile<false>(insts, tiles[blockIdx.x], smem);
+    sweep_one_tile<false>(insts, tiles[blockIdx.x], smem, nullptr);
 }
 
-// Tiles of one walker whose draws lie in device memory.
-__global__ void __launch_bounds__(128) k_sweep_far(const Inst* __restrict__ insts, const Tile* __restrict__ tiles)
+// Tiles of one walker whose draws lie in device memory, 2 kDrawBytes a tile.
+__global__ void __launch_bounds__(128) k_sweep_far(const Inst* __restrict__ insts, const Tile* __restrict__ tiles,
+                                                  char* __restrict__ draws)
 {
     extern __shared__ __align__(16) char smem[];
-    sweep_one_tile<true>(insts, tiles[blockIdx.x], smem);
+    sweep_one_tile<true>(insts, tiles[blockIdx.x], smem, draws + (size_t)blockIdx.x * 2 * kDrawBytes);
 }
 
 // Persistent form: a grid sized to the blocks the GPU holds at once; each block
@@ -383,7 +384,7 @@ __global__ void __launch_bounds__(128) k_sweep_persist(const Inst* __restrict__ 
         const int t = next;
         __syncthreads();
         if (t >= ntiles) break;             // block-uniform: every wave of the grid ends here
-        sweep_one_tile<false>(insts, tiles[t], smem);
+        sweep_one_tile<false>(insts, tiles[t], smem, nullptr);
         __syncthreads();                    // the tile's LDS is free before the next one is staged
     }
 }
