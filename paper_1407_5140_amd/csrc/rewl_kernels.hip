@@ -4,7 +4,8 @@
 //   k_sweep    X single-site attempts per walker, one walker per lane, the
 //              walker's lattice and histogram and its window's ln g base in LDS,
 //              drawn by a second wave (k_sweep_persist: the same from a queue of tiles;
-//              k_sweep_wave: one walker per wave); flatness test in the epilogue
+//              k_sweep_far: with the draws in device memory; k_sweep_wave: one walker
+//              per wave); flatness test in the epilogue
 //   k_merge    per window: when all m walkers are flat, average ln g, reset H,
 //              halve ln f, detect convergence
 //   k_exchange Eq. (1) between neighbouring windows, alternating pairings
@@ -26,7 +27,7 @@ namespace rewl {
 // A block is two waves: wave 0 walks, wave 1 draws the next attempts of its walkers
 // meanwhile, down to the sites whose spins an attempt reads.  (Drawn by the whole GPU in
 // a launch of its own, through a buffer of 12 bytes per attempt in memory, the
-// 65 280-walker batch took 3.9 + 13.1 ms per interval, now 11.3.)
+// 65 280-walker batch took 3.9 + 13.1 ms per interval, now 10.9.)
 // A move changes the bin by at most 2 (Ising) or 4 (Potts), so a proposal
 // outside the window lands in a pad, sees ln g = +inf and is rejected.
 constexpr int kPad = 4;
@@ -511,7 +512,8 @@ __device__ __forceinline__ int ising_d_words(const uint64_t* rows, int wpr, int 
 // attempts, us, with FP64 steps / 34 instructions / now: Ising L=32, 128 walkers 1090 / 695
 // / 554; L=64, 1024: 1100 / 656 / 517; L=128, 2048: 1249 / 811 / 608; Potts q=10 L=32, 4096
 // (4 to a SIMD): 1699 / 970 / 633; L=64, 4096: 1725 / 1180 / 821 (the last three by the
-// order of the blocks too, order_tiles).
+// order of the blocks too, order_tiles).  All with the walkers spread over their windows; a
+// run's first 40 intervals are shorter (Potts L=32 547, L=64 637).
 template <int MODEL, bool WIDE, bool HG>
 __device__ void sweep_wave(const Inst& I, const Tile& tile, char* smem, uint32_t* __restrict__ cost)
 {
