@@ -26,7 +26,7 @@ def flags_at(address):
     return None
 
 
-def test_checkpoint_leaves_the_callers_mapping_alone(rw):
+def test_checkpoint_leaves_the_callers_mapping_alone(rw, monkeypatch):
     gpu = rw.Rewl([rw.make_config(model="ising", L=64, n_windows=16, m=64, X=50, kfinal=12)])
     gpu.run(1)
     n = ctypes.c_size_t(0)
@@ -37,10 +37,14 @@ def test_checkpoint_leaves_the_callers_mapping_alone(rw):
     before = flags_at(at + (3 << 20))
     assert rw._lib.rewl_checkpoint(gpu.h, ctypes.c_void_p(at), ctypes.byref(n)) == rw.REWL_OK
     assert flags_at(at + (3 << 20)) == before and "hg" not in before
+    # the Python call's own 7.7 MB may lie among other blocks: faulted in, not marked
+    asked, real = [], rw._madvise
+    monkeypatch.setattr(rw, "_madvise", lambda lo, size, advice: (asked.append((lo, size, advice)), real(lo, size, advice))[1])
     blob = rw.rewl_checkpoint(gpu.h)
+    at = ctypes.cast(ctypes.c_char_p(blob), ctypes.c_void_p).value
     assert m[: n.value] == blob
-    where = ctypes.cast(ctypes.c_char_p(blob), ctypes.c_void_p).value + (3 << 20)
-    assert "hg" not in flags_at(where)                       # nor does this one of 7.7 MB keep a mark
+    assert [a for _, _, a in asked] == [rw._POPULATE_WRITE]
+    assert all(at <= lo and lo + size <= at + len(blob) and lo % 4096 == size % 4096 == 0 for lo, size, _ in asked)
     gpu.close()
 
 
